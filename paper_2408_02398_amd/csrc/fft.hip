@@ -19,13 +19,22 @@ namespace {
 constexpr int kRowsX = 16;  // real rows per workgroup in the X passes (packed in pairs)
 constexpr int kRowsC = 32;  // the same in the inverse X pass: its input columns are read in 256-byte pieces
 
+// Tile element (z, y, x) of batch b, read at the nearest source voxel: the
+// address is always in bounds, so a thread's loads need no branch and are in
+// flight together (behind a bounds branch each load waited for the one before:
+// 15 us for a 96^3 tile's X pass, 4 us without).  src_value then puts 0 where
+// the element lies outside the source, centres it and squares it.
 __device__ __forceinline__ float load_src(const RealSrc& s, int b, int z, int y, int x) {
+  const int gz = min(max(s.oz + z, 0), s.dz - 1), gy = min(max(s.oy + y, 0), s.dy - 1),
+            gx = min(max(s.ox + x, 0), s.dx - 1);
+  return s.p[b * s.batch_stride + ((size_t)gz * s.dy + gy) * s.dx + gx];
+}
+__device__ __forceinline__ float src_value(const RealSrc& s, int b, int z, int y, int x, float v,
+                                           double center) {
   const int gz = s.oz + z, gy = s.oy + y, gx = s.ox + x;
-  if (gz < 0 || gz >= s.dz || gy < 0 || gy >= s.dy || gx < 0 || gx >= s.dx) return 0.0f;
-  float v = s.p[b * s.batch_stride + ((size_t)gz * s.dy + gy) * s.dx + gx];
-  if (s.center) v = (float)((double)v - s.center[0]);
+  if (s.center) v = (float)((double)v - center);
   if (s.square || (s.square_odd && (b & 1))) v = v * v;
-  return v;
+  return gz < 0 || gz >= s.dz || gy < 0 || gy >= s.dy || gx < 0 || gx >= s.dx ? 0.0f : v;
 }
 
 // Workgroups go to the 8 XCDs in turn (workgroup i to XCD i mod 8), and each
@@ -63,6 +72,7 @@ __global__ __launch_bounds__(kRowsX / 2 * Plan<N>::T) void k_r2c_x(RealSrc src, 
   {
     constexpr int NTH = NP * T, IT = kRowsX * N / NTH;
     static_assert(kRowsX * N % NTH == 0, "tile rows");
+    const double center = src.center ? src.center[0] : 0.0;
     float ld[IT];  // all loads in flight, then the LDS stores
 #pragma unroll
     for (int i = 0; i < IT; ++i) {
@@ -72,7 +82,7 @@ __global__ __launch_bounds__(kRowsX / 2 * Plan<N>::T) void k_r2c_x(RealSrc src, 
 #pragma unroll
     for (int i = 0; i < IT; ++i) {
       const int e = tid + i * NTH;
-      rows[(e / N) * RS + e % N] = ld[i];
+      rows[(e / N) * RS + e % N] = src_value(src, b, z, y0 + e / N, e % N, ld[i], center);
     }
   }
   __syncthreads();
