@@ -10,6 +10,8 @@
 // for all components; each template column's z transform formed in registers
 // from its L stored values), Y pass, X pass with the C2R merge, 1/N^3 scale,
 // weight map, crop and dtype conversion fused into the store.
+#include <algorithm>
+
 #include "internal.hpp"
 
 namespace ttm {
@@ -22,7 +24,7 @@ constexpr int kRowsC = 32;  // the same in the inverse X pass: its input columns
 // Tile element (z, y, x) of batch b, read at the nearest source voxel: the
 // address is always in bounds, so a thread's loads need no branch and are in
 // flight together (behind a bounds branch each load waited for the one before:
-// 15 us for a 96^3 tile's X pass, 4 us without).  src_value then puts 0 where
+// 14 us for a 96^3 tile's X pass, 9 us without).  src_value then puts 0 where
 // the element lies outside the source, centres it and squares it.
 __device__ __forceinline__ float load_src(const RealSrc& s, int b, int z, int y, int x) {
   const int gz = min(max(s.oz + z, 0), s.dz - 1), gy = min(max(s.oy + y, 0), s.dy - 1),
@@ -204,15 +206,18 @@ __device__ __forceinline__ void buffer_store_cf(cf v, __amdgpu_buffer_rsrc_t r, 
 // after its transformed columns are.  The planes of component a + 1 load
 // while component a is transformed.  Grid y picks one of several G spectra
 // (g_stride apart) for a one-component product: its output is work
-// spectrum blockIdx.y.
+// spectrum blockIdx.y.  Grid z splits the components: workgroup z takes
+// components z * ac .. z * ac + ac - 1 (see inverse_n).
 template <int N, int JP>
 __global__ __launch_bounds__((ZinvBlock<N, JP>::CB * Plan<N>::T)) void k_zinv_mul(
     const cf* __restrict__ G, const cf* __restrict__ P, size_t p_stride, int sp, int A,
     const double* __restrict__ center, cf* __restrict__ out, size_t out_stride, int z_limit,
-    const cf* __restrict__ tw, size_t g_stride) {
+    const cf* __restrict__ tw, size_t g_stride, int ac) {
   constexpr int T = Plan<N>::T, E = N / T, CB = ZinvBlock<N, JP>::CB, NC = (N / 2 + 1) * N;
   G += blockIdx.y * g_stride;
-  out += blockIdx.y * out_stride;
+  out += (blockIdx.y + (size_t)blockIdx.z * ac) * out_stride;
+  P += blockIdx.z * ac * p_stride;
+  A = min(ac, A - (int)blockIdx.z * ac);
   constexpr int S = lds_stride<N>();
   constexpr int SB = CB + 1;                // staging row: CB columns, one pad element
   constexpr int ZP = JP > 0 ? JP * T : 1;   // staged template planes
@@ -486,9 +491,18 @@ int inverse_n(const cf* G, const cf* Sp, size_t s_stride, int s_planes, int A, c
     jp = N == 512 ? 2 : 1;
     while (jp < E && jp * T < s_planes) jp *= 2;
   }
+  // Few columns (a 96^3 tile has 294 workgroups of two wavefronts) leave the
+  // chip idle while every workgroup walks all A components, so the components
+  // are split until 4096 workgroups are in the grid; at least 4 components stay
+  // together (2 where the columns alone do not give each CU a workgroup),
+  // because each part reads G again.  K = 28: 96^3 75 -> 45 us, 128^3 75 -> 62 us,
+  // 256^3 571 -> 549 us, 64^3 (K = 15) 19 -> 8.5 us; 512^3 is not split.
   auto launch = [&](auto kern, int cb) {
-    hipLaunchKernelGGL(kern, dim3(NROWS / cb, gb), dim3(cb * T), 0, s, G, Sp, s_stride, s_planes, A,
-                       center, work, work_stride, zlim, tw, g_stride);
+    const int nblk = NROWS / cb, least = nblk < 256 ? 2 : 4;
+    const int parts = std::max(1, std::min((A + least - 1) / least, 4096 / nblk + (4096 % nblk != 0)));
+    const int ac = nblk < 4096 ? (A + parts - 1) / parts : A;
+    hipLaunchKernelGGL(kern, dim3(nblk, gb, (A + ac - 1) / ac), dim3(cb * T), 0, s, G, Sp, s_stride,
+                       s_planes, A, center, work, work_stride, zlim, tw, g_stride, ac);
   };
   constexpr int J2 = 2 < E ? 2 : E, J4 = 4 < E ? 4 : E, J8 = 8 < E ? 8 : E;
   switch (jp) {
