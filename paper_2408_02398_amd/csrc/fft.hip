@@ -305,6 +305,162 @@ __global__ __launch_bounds__((ZinvBlock<N, JP>::CB * Plan<N>::T)) void k_zinv_mu
   }
 }
 
+// ------------------------------------------------- Y and X inverse of a plane
+// For N <= 160 one workgroup takes a whole (kx, ky) plane of one work spectrum
+// -- contiguous in memory -- through the inverse Y transforms of its N/2 + 1
+// rows and the inverse X transforms of its row pairs, so the plane is read once
+// and only the cropped, scaled real rows are written: 2 N (N/2 + 1) * 8 bytes per
+// plane less than a Y pass and an X pass of their own move.  Bound by its own
+// latency (load, transforms and stores of one plane follow each other, and the
+// LDS holds one to three planes per CU): K = 28, 96^3 64 -> 47 us, 128^3 (97^3
+// crop) 140 -> 101 us.  Between the two transforms the
+// plane sits in LDS as [kx][y].  PITCH (elements per kx row) holds a row's
+// exchange area (N + N/16) and is 4 or 12 mod 32, so the 16-byte reads of a
+// row pair (y, y + 1) by T consecutive kx fall on different banks.
+// The same one-dimensional transforms run as in the separate passes: same bits.
+template <int N> struct PlaneWg {
+  static constexpr int NTH = ((N / 2 + 1) * Plan<N>::T + 63) / 64 * 64;       // every row at once
+  static constexpr int EU = N <= 64 ? 4 : N <= 128 ? 5 : 3;                  // wavefronts per SIMD
+};
+template <int N> __host__ __device__ constexpr int plane_pitch() { return N == 32 ? 36 : N + 12; }
+constexpr int kOutPad = 4;   // floats added to an output row in LDS
+
+// Packed spectrum A + iB of the pair of real rows (2p, 2p + 1) at index n, from
+// the plane in LDS (only kx <= N/2 is stored).
+template <int N, int PITCH>
+__device__ __forceinline__ cf pair_bin(const cf* plane, int p, int n) {
+  const int m = n <= N / 2 ? n : N - n;
+  const float4 q = *reinterpret_cast<const float4*>(plane + m * PITCH + 2 * p);
+  cf a = cf{q.x, q.y}, b = cf{q.z, q.w};
+  if (m == 0 || m == N / 2) {  // spectra of real rows: these bins are real
+    a.y = 0.0f;
+    b.y = 0.0f;
+  }
+  if (n > N / 2) {
+    a = cconj(a);
+    b = cconj(b);
+  }
+  return cf{a.x - b.y, a.y + b.x};  // A + iB
+}
+
+// Output rows 0 .. dst.sy - 1 of plane z, batch b, from LDS rows of N + kOutPad
+// floats: scaled, weighted, converted.  Short rows (N <= 96) are dealt out voxel
+// by voxel, UN weight-map loads in flight per thread; from 128 on a wavefront
+// takes every NW-th row, 64 columns of all its rows at a time, so the row bases
+// stay in scalar registers (a short row would leave half the lanes idle: whole
+// 96^3 tile 172 us against 166, 128^3 tiles 1763 us against 1712 the other way).
+template <int N, int NTH>
+__device__ __forceinline__ void store_rows(const float* orow, const RealDst& dst, int b, int z, int tid) {
+  constexpr int RS = N + kOutPad, NW = NTH / 64;
+  const int nr = dst.sy, sx = dst.sx;
+  const float* wr = dst.w ? dst.w + ((size_t)(dst.woz + z) * dst.wy + dst.woy) * dst.wx + dst.wox : nullptr;
+  const size_t o0 = b * dst.batch_stride + ((size_t)(dst.vz0 + z) * dst.by + dst.vy0) * dst.bx + dst.vx0;
+  auto put = [&](size_t row, int x, float v) {
+    if (dst.dtype == 1) {
+      (reinterpret_cast<unsigned short*>(dst.p) + o0 + row)[(unsigned)x] = f32_to_bf16(v);
+    } else {
+      (reinterpret_cast<float*>(dst.p) + o0 + row)[(unsigned)x] = v;
+    }
+  };
+  if constexpr (N <= 96) {
+    constexpr int UN = 6;
+    const int total = nr * sx, dr = NTH / sx, dx = NTH - dr * sx;
+    int r = tid / sx, x = tid - r * sx;
+    for (int i0 = tid; i0 < total; i0 += UN * NTH) {
+      float val[UN], wv[UN];
+      int rr[UN], xx[UN];
+#pragma unroll
+      for (int k = 0; k < UN; ++k) {
+        rr[k] = min(r, nr - 1);    // past the end: a row that exists, not stored
+        xx[k] = x;
+        wv[k] = wr ? wr[(size_t)rr[k] * dst.wx + x] : 1.0f;
+        val[k] = orow[rr[k] * RS + x] * dst.scale;
+        r += dr;
+        x += dx;
+        if (x >= sx) {
+          x -= sx;
+          ++r;
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < UN; ++k)
+        if (i0 + k * NTH < total) put((size_t)rr[k] * dst.bx, xx[k], wr ? val[k] * wv[k] : val[k]);
+    }
+  } else {
+    constexpr int UN = (N + NW - 1) / NW;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int x = tid & 63; x < sx; x += 64) {
+      float wv[UN];
+      if (wr) {
+#pragma unroll
+        for (int k = 0; k < UN; ++k)   // rows past the end: the last one, not stored
+          wv[k] = (wr + (size_t)min(wave + k * NW, nr - 1) * dst.wx)[(unsigned)x];
+      }
+#pragma unroll
+      for (int k = 0; k < UN; ++k) {
+        const int r = wave + k * NW;
+        if (r >= nr) break;
+        const float v = orow[r * RS + x] * dst.scale;
+        put((size_t)r * dst.bx, x, wr ? v * wv[k] : v);
+      }
+    }
+  }
+}
+
+// The whole plane in LDS (111 KB at 160).
+template <int N>
+__global__ __launch_bounds__(PlaneWg<N>::NTH) __attribute__((amdgpu_waves_per_eu(PlaneWg<N>::EU))) void k_c2r_plane(const cf* __restrict__ spec,
+                                                               size_t spec_stride, int A, RealDst dst,
+                                                               const cf* __restrict__ tw) {
+  constexpr int T = Plan<N>::T, E = N / T, NH = N / 2 + 1, NTH = PlaneWg<N>::NTH, PITCH = plane_pitch<N>();
+  constexpr int S = lds_stride<N>(), RS = N + kOutPad;
+  constexpr int B1 = NH * PITCH * 8, B2 = N / 2 * S * 8, B3 = N * RS * 4;
+  constexpr int BYTES = B1 > B2 ? (B1 > B3 ? B1 : B3) : (B2 > B3 ? B2 : B3);
+  static_assert(64 % T == 0 && PITCH % 2 == 0 && PITCH >= N + N / 16 && BYTES <= 160 * 1024, "plane layout");
+  __shared__ __align__(16) unsigned char smem[BYTES];
+  cf* plane = reinterpret_cast<cf*>(smem);
+  cf* xl = reinterpret_cast<cf*>(smem);
+  float* orow = reinterpret_cast<float*>(smem);
+  const int tid = threadIdx.x, q = tid / T, t = tid % T;
+  // component fastest: the workgroups that share a plane's weight-map rows run
+  // together in one XCD
+  const int item = (int)xcd_item(blockIdx.x, gridDim.x);
+  const int b = item % A, z = item / A;
+  const cf* in = spec + b * spec_stride + (size_t)z * NH * N;
+  FftTw<N> twr;
+  cf v[E];
+  const int row = min(q, NH - 1);                   // the last wavefront's spare lanes read a row that exists
+#pragma unroll
+  for (int j = 0; j < E; ++j) v[j] = at_byte(in, (unsigned)(row * N + t + T * j) * 8u);
+  twr.load(tw, t);
+  if (q < NH) {
+    cf* mine = plane + q * PITCH;                   // each row's transform lies in one wavefront
+    fft_1d<N, true, true>(v, mine, twr, t);
+#pragma unroll
+    for (int j = 0; j < E; ++j) mine[t + T * j] = v[j];
+    // the row paired with the last kept one in one complex transform is zero
+    if ((dst.sy & 1) && t == dst.sy % T) mine[dst.sy] = cf{0.0f, 0.0f};
+  }
+  __syncthreads();
+  const bool live = 2 * q < dst.sy;                 // pair q holds a kept row
+  if (live) {
+#pragma unroll
+    for (int j = 0; j < E; ++j) v[j] = pair_bin<N, PITCH>(plane, q, t + T * j);
+  }
+  __syncthreads();  // exchange areas overlap the plane
+  if (live) fft_1d<N, true, true>(v, xl + q * S, twr, t);
+  __syncthreads();  // the rows overlap other pairs' exchange areas
+  if (live) {
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      orow[(2 * q) * RS + t + T * j] = v[j].x;
+      orow[(2 * q + 1) * RS + t + T * j] = v[j].y;
+    }
+  }
+  __syncthreads();
+  store_rows<N, NTH>(orow, dst, b, z, tid);
+}
+
 // ---------------------------------------------------------------- X inverse
 template <int N>
 __global__ __launch_bounds__(kRowsC / 2 * Plan<N>::T) __attribute__((amdgpu_waves_per_eu(N == 512 ? 8 : 1))) void k_c2r_x(const cf* __restrict__ spec,
@@ -514,11 +670,16 @@ int inverse_n(const cf* G, const cf* Sp, size_t s_stride, int s_planes, int A, c
     default: launch(k_zinv_mul<N, E>, ZinvBlock<N, E>::CB); break;
   }
   const int nb = A * gb;  // work spectra written by the Z pass
-  constexpr int RB = (128 / T > 0 ? 128 / T : 1);
-  hipLaunchKernelGGL((k_c2c_rows<N, true>), dim3(NROWS / RB, nb), dim3(RB * T), 0, s, work,
-                     work_stride, zlim, dst.sy, tw);
-  hipLaunchKernelGGL(k_c2r_x<N>, dim3(nb * (N / kRowsC) * N), dim3(kRowsC / 2 * T), 0, s, work,
-                     work_stride, nb, dst, tw);
+  if constexpr (N <= 160) {   // at 192 one plane fills the LDS: 1084 us a tile (K = 28) in two passes, 1148 us in one
+    hipLaunchKernelGGL(k_c2r_plane<N>, dim3(nb * zlim), dim3(PlaneWg<N>::NTH), 0, s, work, work_stride, nb,
+                       dst, tw);
+  } else {
+    constexpr int RB = (128 / T > 0 ? 128 / T : 1);
+    hipLaunchKernelGGL((k_c2c_rows<N, true>), dim3(NROWS / RB, nb), dim3(RB * T), 0, s, work,
+                       work_stride, zlim, dst.sy, tw);
+    hipLaunchKernelGGL(k_c2r_x<N>, dim3(nb * (N / kRowsC) * N), dim3(kRowsC / 2 * T), 0, s, work,
+                       work_stride, nb, dst, tw);
+  }
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? 0 : hip_status(e, "fft inverse launch");
 }
