@@ -57,3 +57,49 @@ def test_field_at_tile_edges(T, ctx, N, n, L, shape, bf16):
         ref = torch.fft.irfftn(G * torch.fft.rfftn(Tt[k].cuda().double(), s=shape).conj(), s=shape)
         ref = wv * ref[:size[0], :size[1], :size[2]]
         assert _normwise(C[k].double().cpu().numpy(), ref.cpu().numpy()) <= 2e-6 + (2.0 ** -9 if bf16 else 0.0)
+
+
+def _tensor_template(tn, quats, n, d, L):
+    """Alg. 1 in 64 bits: (1/nq) sum_q v_q^alpha t'(c + R_q^T (p - c)), trilinear, 0 outside the box."""
+    import itertools
+
+    from scipy.ndimage import map_coordinates
+    q = quats / np.linalg.norm(quats, axis=1, keepdims=True)
+    w, x, y, z = q.T
+    R = np.array([[1 - 2 * (y * y + z * z), 2 * (x * y - w * z), 2 * (x * z + w * y)],
+                  [2 * (x * y + w * z), 1 - 2 * (x * x + z * z), 2 * (y * z - w * x)],
+                  [2 * (x * z - w * y), 2 * (y * z + w * x), 1 - 2 * (x * x + y * y)]]).transpose(2, 0, 1)
+    v = q if d == 4 else R[:, :, 2]
+    ex = [e for e in itertools.product(range(n, -1, -1), repeat=d) if sum(e) == n]
+    i = np.arange(L) - L // 2
+    zz, yy, xx = np.meshgrid(i, i, i, indexing="ij")
+    p = np.stack([xx, yy, zz], -1).reshape(-1, 3)
+    out = np.zeros((len(ex), L ** 3))
+    pad = np.pad(tn.astype(np.float64), 2)
+    for k in range(len(q)):
+        s = p @ R[k] + L // 2 + 2
+        val = map_coordinates(pad, s[:, ::-1].T, order=1, mode="constant", cval=0.0)
+        out += np.outer([np.prod(v[k] ** np.array(e)) for e in ex], val)
+    return out.reshape(-1, L, L, L) / len(q)
+
+
+@pytest.mark.parametrize("L,r,n,dprime,nq", [
+    (2, 0.9, 2, 3, 3),       # the smallest box: every cell pair is the same one
+    (7, 3.4, 0, 3, 1),       # one component, one rotation; the ball meets the box's faces
+    (12, 5.9, 6, 3, 65),     # a second chunk of one rotation
+    (9, 4.0, 4, 4, 300),     # 35 components: two tiles of 32, chunks on every wavefront
+    (8, 3.5, 8, 4, 70),      # 165 components: three launches
+])
+def test_tensor_template_edges(T, ctx, L, r, n, dprime, nq):
+    """build_tensor against Alg. 1 in 64 bits on its own t': 1e-5 normwise, as the parity test."""
+    import torch
+    rng = np.random.default_rng(L)
+    tmpl = torch.from_numpy(rng.standard_normal((L, L, L)).astype(np.float32)).cuda()
+    quats = rng.standard_normal((nq, 4)).astype(np.float32)
+    Tt, tn = T.build_tensor(ctx, T.make_desc(n, L, r, dprime=dprime), tmpl, torch.from_numpy(quats).cuda())
+    ref = _tensor_template(tn.cpu().numpy(), quats.astype(np.float64), n, dprime, L)
+    got = Tt.cpu().numpy().astype(np.float64)
+    if not np.linalg.norm(ref) > 0.0:
+        assert np.array_equal(got, ref)
+    else:
+        assert _normwise(got, ref) <= 1e-5
