@@ -103,3 +103,34 @@ def test_tensor_template_edges(T, ctx, L, r, n, dprime, nq):
         assert np.array_equal(got, ref)
     else:
         assert _normwise(got, ref) <= 1e-5
+
+
+@pytest.mark.parametrize("n,dprime,B", [(2, 3, 1), (6, 3, 15), (4, 3, 65), (4, 4, 130), (6, 3, 8193), (2, 4, 16400)])
+def test_training_step_edges(T, ctx, n, dprime, B):
+    """train_step's gradients and loss against the oracle's network with BF16
+    operands and activations, for batches that end inside a wavefront's 16
+    samples, a workgroup's 64, and past one and two blocks per workgroup.
+    Bound: 1e-2 normwise, the bound of the gradient parity test (what is left
+    between the two is the BF16 rounding of dY, dZ2 and dZ1 as operands, 2^-9
+    each)."""
+    import torch
+
+    from oracle import mlp as omlp
+    rng = np.random.default_rng(B)
+    K = T.n_components(n, dprime)
+    p = omlp.init_params(rng, K, d_out=dprime)
+    for b in ("b1", "b2", "b3"):
+        p[b] = 0.1 * rng.standard_normal(p[b].shape)
+    C, t = rng.standard_normal((B, K)), rng.standard_normal((B, dprime))
+    flat = omlp.pad_params(p, K, dprime).astype(np.float32)
+    net = T.MLP(ctx, T.make_desc(n, 16, 7.0, dprime=dprime), torch.from_numpy(flat).cuda())
+    grads = torch.empty(net.n_params, device="cuda")
+    before = net.params.clone()
+    loss = net.train_step(torch.from_numpy(C.astype(np.float32)).cuda(), torch.from_numpy(t.astype(np.float32)).cuda(),
+                          lr=0.0, grads=grads)
+    assert torch.equal(net.params, before)
+    pr = {k: (omlp.bf16_round(v) if k.startswith("W") else v) for k, v in p.items()}
+    y, cache = omlp.forward(pr, omlp.features(C, n, dprime), bf16=True)
+    ref = omlp.pad_params(omlp.backward(pr, cache, t), K, dprime)
+    assert float(loss) == pytest.approx(omlp.loss(y, t), rel=1e-3)
+    assert _normwise(grads.cpu().numpy().astype(np.float64), ref) <= 1e-2
