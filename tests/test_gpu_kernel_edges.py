@@ -134,3 +134,60 @@ def test_training_step_edges(T, ctx, n, dprime, B):
     ref = omlp.pad_params(omlp.backward(pr, cache, t), K, dprime)
     assert float(loss) == pytest.approx(omlp.loss(y, t), rel=1e-3)
     assert _normwise(grads.cpu().numpy().astype(np.float64), ref) <= 1e-2
+
+
+@pytest.mark.parametrize("L,r,n,n_peaks,rs", [
+    (11, 4.0, 2, 3, 1.0),     # rows shorter than a block of 16, a wavefront per component tile
+    (16, 6.0, 4, 140, 1.5),   # whole blocks, one wavefront for all component tiles (19 candidates)
+    (35, 15.0, 2, 2, 2.0),    # rows of 2 blocks and 3 voxels; the template too large for LDS
+    (18, 7.0, 6, 70, 3.0),    # 84 components, 123 candidates: the second block of tiles is partly empty
+])
+def test_refine_field_and_lncc_edges(T, ctx, L, r, n, n_peaks, rs):
+    """refine at its tile edges: the LNCC it returns at the peaks against Eq. lncc
+    at the rotation it returns, in 64 bits, and that rotation's lambda against the
+    best over many rotations of the exact field (Eq. tcc).  Bounds: 1e-4 of the
+    LNCC scale, the bound of the refinement parity test."""
+    import torch
+
+    import synth
+    from oracle import ttm as orc
+    rng = np.random.default_rng(L)
+    shape = (L + 12, L + 9, L + 14)
+    tmpl = synth.blob_template(np.random.default_rng(1), L, 3).volume().astype(np.float32)
+    vol = rng.standard_normal(shape).astype(np.float32)
+    vol[2:2 + L, 3:3 + L, 4:4 + L] += 4.0 * tmpl / tmpl.max()
+    d = T.make_desc(n, L, r, dprime=4)
+    Q = synth.rotation_samples(3)
+    Tt, tn = T.build_tensor(ctx, d, torch.from_numpy(tmpl).cuda(), torch.from_numpy(Q).float().cuda())
+    N = 64
+    spec = T.template_spectra(ctx, d, Tt, N)
+    g, w, stats = T.normalize(ctx, d, torch.from_numpy(vol).cuda(), spec, N)
+    lo, hi = T.valid_bounds(shape, L)
+    peaks = np.stack([rng.integers(a, b + 1, n_peaks) for a, b in zip(lo, hi)], 1).astype(np.int32)
+    starts = torch.from_numpy(synth.start_vectors(count=16, dim=4)).cuda()
+    out = T.refine(ctx, d, g, w, Tt, tn, torch.from_numpy(peaks).cuda(), starts, r_s=rs)
+    g64, w64, tn64, T64 = (a.double().cpu().numpy() for a in (g, w, tn, Tt))
+    c = L // 2
+    qp, lp = out["quat_peak"].cpu().numpy().astype(np.float64), out["lncc_peak"].cpu().numpy()
+    pos, qr, lr = out["pos"].cpu().numpy(), out["quat"].cpu().numpy().astype(np.float64), out["lncc"].cpu().numpy()
+    probe = synth.random_quaternions(np.random.default_rng(2), 400)
+    for i in range(0, n_peaks, max(1, n_peaks // 6)):
+        for (z, y, x), q, l in ((peaks[i], qp[i], lp[i]), (pos[i], qr[i], lr[i])):
+            win = g64[z - c:z - c + L, y - c:y - c + L, x - c:x - c + L]
+            wv = w64[z, y, x]
+            from scipy.ndimage import map_coordinates
+            a, b, e, f = q / np.linalg.norm(q)
+            R = np.array([[1 - 2 * (e * e + f * f), 2 * (b * e - a * f), 2 * (b * f + a * e)],
+                          [2 * (b * e + a * f), 1 - 2 * (b * b + f * f), 2 * (e * f - a * b)],
+                          [2 * (b * f - a * e), 2 * (e * f + a * b), 1 - 2 * (b * b + e * e)]])
+            k = np.arange(L) - c
+            zz, yy, xx = np.meshgrid(k, k, k, indexing="ij")
+            s = np.stack([xx, yy, zz], -1).reshape(-1, 3) @ R + c + 2
+            rot = map_coordinates(np.pad(tn64, 2), s[:, ::-1].T, order=1, mode="constant")
+            scale = wv * np.linalg.norm(win)
+            assert abs(l - wv * float(rot @ win.ravel())) <= 1e-4 * max(scale, 1.0)
+            C = wv * (T64.reshape(len(T64), -1) @ win.ravel())
+            lam = orc.sym.inner_power(C, q / np.linalg.norm(q), n)
+            best = max(float(orc.sym.inner_power(C, p, n)) for p in probe)
+            assert float(lam) >= best - 1e-4 * float(orc.sym.frobenius(C, n, 4))
+    assert np.all(lr >= lp)
