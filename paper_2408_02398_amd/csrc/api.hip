@@ -171,35 +171,49 @@ __global__ void k_mask(float* __restrict__ m, int L, float r) {
   m[i] = ((float)(x * x + y * y + z * z) <= r * r) ? 1.0f : 0.0f;
 }
 
-// t' = m (S(t) - mu) / sigma_t, S(t) = m (h * t) with zero padding (Eq. norm_t).
-// One workgroup; the box has at most 64^3 voxels.
-__global__ __launch_bounds__(1024) void k_template_norm(const float* __restrict__ t, int L, float r,
-                                                        float a, float* __restrict__ tn) {
-  const int n = L * L * L, c = L / 2;
+// t' = m (S(t) - mu) / sigma_t, S(t) = m (h * t) with zero padding (Eq. norm_t), in
+// two kernels: S(t) over the whole chip, every thread's 27 loads in flight
+// together, then one workgroup for its sums and the scaling (the box has at most
+// 64^3 voxels).  In one workgroup with each neighbour behind its bounds branch,
+// 40^3 took 200 us; now 69 us.
+__global__ __launch_bounds__(256) void k_template_filter(const float* __restrict__ t, int L, float r, float a,
+                                                         float* __restrict__ tn) {
+  const int i = blockIdx.x * 256 + threadIdx.x, c = L / 2;
+  if (i >= L * L * L) return;
   const float w0 = a, w1 = 1.0f - 2.0f * a;
-  double sm = 0.0, s1 = 0.0, s2 = 0.0, mm = 0.0;
-  for (int i = threadIdx.x; i < n; i += 1024) {
-    const int x = i % L, y = (i / L) % L, z = i / (L * L);
-    const int dx = x - c, dy = y - c, dz = z - c;
-    const bool in = (float)(dx * dx + dy * dy + dz * dz) <= r * r;
-    float st = 0.0f;
-    if (in) {
-      for (int k = -1; k <= 1; ++k) {
-        const int zz = z + k;
-        if (zz < 0 || zz >= L) continue;
-        for (int j = -1; j <= 1; ++j) {
-          const int yy = y + j;
-          if (yy < 0 || yy >= L) continue;
-          const float* row = t + ((size_t)zz * L + yy) * L;
-          float hx = w1 * row[x];
-          if (x > 0) hx += w0 * row[x - 1];
-          if (x < L - 1) hx += w0 * row[x + 1];
-          st += (k == 0 ? w1 : w0) * (j == 0 ? w1 : w0) * hx;
-        }
-      }
-      mm += 1.0;
+  const int x = i % L, y = (i / L) % L, z = i / (L * L);
+  const int dx = x - c, dy = y - c, dz = z - c;
+  float st = 0.0f;
+  if ((float)(dx * dx + dy * dy + dz * dz) <= r * r) {
+    float v[9][3];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+      const int zz = z + k / 3 - 1, yy = y + k % 3 - 1;
+      const float* row = t + ((size_t)min(max(zz, 0), L - 1) * L + min(max(yy, 0), L - 1)) * L;
+      v[k][0] = row[max(x - 1, 0)];
+      v[k][1] = row[x];
+      v[k][2] = row[min(x + 1, L - 1)];
     }
-    tn[i] = st;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+      const int kz = k / 3 - 1, ky = k % 3 - 1, zz = z + kz, yy = y + ky;
+      float hx = w1 * v[k][1];
+      if (x > 0) hx += w0 * v[k][0];
+      if (x < L - 1) hx += w0 * v[k][2];
+      if (zz >= 0 && zz < L && yy >= 0 && yy < L) st += (kz == 0 ? w1 : w0) * (ky == 0 ? w1 : w0) * hx;
+    }
+  }
+  tn[i] = st;
+}
+
+__global__ __launch_bounds__(1024) void k_template_norm(int L, float r, float* __restrict__ tn) {
+  const int n = L * L * L, c = L / 2;
+  double sm = 0.0, s1 = 0.0, s2 = 0.0, mm = 0.0;
+#pragma unroll 8
+  for (int i = threadIdx.x; i < n; i += 1024) {
+    const int x = i % L - c, y = (i / L) % L - c, z = i / (L * L) - c;
+    const float st = tn[i];
+    if ((float)(x * x + y * y + z * z) <= r * r) mm += 1.0;
     sm += (double)st;          // <S(t), m> = <S(t), 1> for a binary mask
     s2 += (double)st * (double)st;
   }
@@ -230,11 +244,19 @@ __global__ __launch_bounds__(1024) void k_template_norm(const float* __restrict_
     inv_sig = var > 0.0 ? 1.0 / sqrt(var) : 0.0;
   }
   __syncthreads();
+#pragma unroll 8
   for (int i = threadIdx.x; i < n; i += 1024) {
     const int x = i % L - c, y = (i / L) % L - c, z = i / (L * L) - c;
     const bool in = (float)(x * x + y * y + z * z) <= r * r;
     tn[i] = in ? (float)(((double)tn[i] - mu_s) * inv_sig) : 0.0f;
   }
+}
+
+void template_norm(const ttm_desc* d, const float* tmpl, float* tn, hipStream_t s) {
+  const int L = d->L;
+  hipLaunchKernelGGL(k_template_filter, dim3((L * L * L + 255) / 256), dim3(256), 0, s, tmpl, L, d->mask_radius,
+                     d->filter_a, tn);
+  hipLaunchKernelGGL(k_template_norm, dim3(1), dim3(1024), 0, s, L, d->mask_radius, tn);
 }
 
 constexpr int kMaxK = 165;    // n = 8, d' = 4
@@ -429,6 +451,210 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_build(const float* __restr
     const int k = 32 * b + 8 * (i >> 2) + 4 * (l >> 5) + (i & 3), p = vox[l & 31];
     double s = 0.0;
     for (int w = 0; w < kBuildWaves; ++w) s += red[(w * MB * 16) * 64 + e];
+    if (k < na && p >= 0) T[(size_t)(a0 + k) * n + p] = (float)(s * inv);
+  }
+}
+
+// k_build with t' in LDS, for balls that fit it (kBuildBall floats, r up to 17):
+// the gathers of t' then cost LDS cycles instead of L2 lines.
+//
+// Slice dz of the ball is kept as the square |dy| <= h + 1, -h - 2 <= dx <= h + 2
+// around its disc of half-width h, its border 0, so a cell outside the ball is
+// read from the border by clamping its indices; an empty slice at either end.
+// Row pitches 2 h + 5 are odd: a rotated row of samples can run along any axis.
+// A workgroup of 16 wavefronts fills a CU: wavefront w takes voxel group w % 4 (32
+// voxels) and every fourth block of kLdsChunk rotations, whose monomials the four
+// wavefronts of a group share; the totals meet in LDS at the end as in k_build.
+// 40^3, r = 17, 24 000 rotations, K = 28: 3.1 ms, 6.6 ms from global memory.
+constexpr int kLdsChunk = 32;
+constexpr int kLdsWaves = 16;
+constexpr int kLdsGroups = 4;                     // rotation groups = voxel groups
+constexpr int kBuildBall = 34816;
+constexpr int kBuildSlices = 64;
+
+// half-width of the ball's slice dz: the largest h with h^2 + dz^2 <= r^2, -1: none
+__host__ __device__ inline int slice_half(float r, int dz) {
+  int h = -1;
+  while ((float)((h + 1) * (h + 1) + dz * dz) <= r * r) ++h;
+  return h;
+}
+__host__ __device__ inline int slice_floats(int h) { return (2 * h + 3) * (2 * h + 5); }
+
+__global__ __launch_bounds__(64 * kLdsWaves) void k_build_lds(const float* __restrict__ tn, int L, float r, int lim2,
+                                                             const float* __restrict__ quats, int nq,
+                                                             int dprime, float ax, float ay, float az,
+                                                             int a0, int na, Exponents ex,
+                                                             float* __restrict__ T) {
+  constexpr int NT = 64 * kLdsWaves;
+  struct Chunk {
+    float mono[kLdsChunk][32];    // v_q^a, rotated by the row
+    float rot[kLdsChunk][12];
+  };
+  __shared__ __align__(16) float ball[kBuildBall];
+  __shared__ __align__(16) Chunk chunks[kLdsGroups];
+  __shared__ int2 slice[kBuildSlices];            // {place of (dy, dx) = 0, h}
+  __shared__ int vox[kLdsGroups * kBuildVox];
+  static_assert(kLdsWaves * 16 * 64 * 8 <= sizeof(ball), "totals fit the ball's memory");
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int grp = wave / kLdsGroups, sub = wave % kLdsGroups;   // rotation group, voxel group
+  const int c = L / 2, R = (int)floorf(r);
+  // this workgroup's voxels: 128 b .. 128 b + 127 of the reachable ones, in box order
+  int* part = reinterpret_cast<int*>(ball);
+  const int rows = L * L, per = (rows + NT - 1) / NT;
+  int cnt = 0;
+  for (int i = tid * per; i < min(rows, (tid + 1) * per); ++i) {
+    int x0;
+    cnt += row_reach(lim2, L, i / L, i % L, x0);
+  }
+  part[tid] = cnt;
+  if (tid < kLdsGroups * kBuildVox) vox[tid] = -1;
+  __syncthreads();
+  if (tid < 64) {                                 // exclusive scan, a run of counts per lane
+    int own = 0;
+    for (int i = 0; i < NT / 64; ++i) own += part[tid * (NT / 64) + i];
+    int run = own;
+    for (int off = 1; off < 64; off <<= 1) {
+      const int v = __shfl_up(run, off);
+      if (tid >= off) run += v;
+    }
+    run -= own;
+    for (int i = 0; i < NT / 64; ++i) {
+      const int v = part[tid * (NT / 64) + i];
+      part[tid * (NT / 64) + i] = run;
+      run += v;
+    }
+  }
+  __syncthreads();
+  int before = part[tid];
+  const int first = blockIdx.x * kLdsGroups * kBuildVox;
+  if (before < first + kLdsGroups * kBuildVox && before + cnt > first) {
+    for (int i = tid * per; i < min(rows, (tid + 1) * per); ++i) {
+      int x0;
+      const int m = row_reach(lim2, L, i / L, i % L, x0);
+      for (int k = max(0, first - before); k < m && before + k < first + kLdsGroups * kBuildVox; ++k)
+        vox[before + k - first] = i * L + x0 + k;
+      before += m;
+    }
+  }
+  __syncthreads();
+  if (tid == 0) {
+    int at = 0;
+    for (int z = -R - 1; z <= R + 1; ++z) {
+      const int h = slice_half(r, z);
+      slice[z + R + 1] = make_int2(at + (h + 1) * (2 * h + 5) + h + 2, h);
+      at += slice_floats(h);
+    }
+  }
+  __syncthreads();
+  for (int z = -R - 1 + wave; z <= R + 1; z += kLdsWaves) {
+    const int2 s = slice[z + R + 1];
+    const int h = s.y, p = 2 * h + 5, n = slice_floats(h);
+    float* out = ball + s.x - (h + 1) * p - (h + 2);
+    for (int e = lane; e < n; e += 64) {
+      const int y = e / p - (h + 1), x = e % p - (h + 2);
+      const bool in = abs(y) <= h && abs(x) <= h && z + c >= 0 && z + c < L && y + c >= 0 && y + c < L &&
+                      x + c >= 0 && x + c < L;
+      out[e] = in ? tn[((size_t)(z + c) * L + (y + c)) * L + (x + c)] : 0.0f;
+    }
+  }
+  const int my = vox[sub * kBuildVox + (lane & 31)], mv = my < 0 ? 0 : my;
+  const float px = (float)(mv % L - c), py = (float)((mv / L) % L - c), pz = (float)(mv / (L * L) - c);
+  Chunk& ch = chunks[grp];
+  double acc[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] = 0.0;
+  f32x16 sum;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) sum[i] = 0.0f;
+  int held = 0;                                   // rotations in sum
+  const int steps = (nq + kLdsGroups * kLdsChunk - 1) / (kLdsGroups * kLdsChunk);
+  for (int st = 0; st < steps; ++st) {
+    const int q0 = (st * kLdsGroups + grp) * kLdsChunk;
+    __syncthreads();                              // the last block's reads are done (and the ball is filled)
+    {
+      // lane: rotation lane % 32 of the block; the group's wavefronts and the two
+      // lanes of a rotation share out the components (0 past the last rotation)
+      const int ql = lane & 31, part4 = 2 * sub + (lane >> 5);
+      const bool live = q0 + ql < nq;
+      float Rm[9], qn[4], v[4];
+      quat_rotation(quats + 4 * (size_t)min(q0 + ql, nq - 1), Rm, qn);
+      if (dprime == 4) {
+        v[0] = qn[0]; v[1] = qn[1]; v[2] = qn[2]; v[3] = qn[3];
+      } else {
+        v[0] = Rm[0] * ax + Rm[1] * ay + Rm[2] * az;
+        v[1] = Rm[3] * ax + Rm[4] * ay + Rm[5] * az;
+        v[2] = Rm[6] * ax + Rm[7] * ay + Rm[8] * az;
+        v[3] = 1.0f;
+      }
+      if (part4 == 0) {
+#pragma unroll
+        for (int k = 0; k < 9; ++k) ch.rot[ql][k] = Rm[k];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        // component 4 part4 + i; the exponents of the lanes' two halves differ, so
+        // each factor is taken while the half's own count lasts
+        const int k = 4 * part4 + i, k0 = 8 * sub + i, k1 = k0 + 4;
+        float m = live && k < na ? 1.0f : 0.0f;
+        for (int d = 0; d < dprime; ++d) {
+          const int e0 = k0 < na ? ex.e[a0 + k0][d] : 0, e1 = k1 < na ? ex.e[a0 + k1][d] : 0;
+          const int mine = lane < 32 ? e0 : e1;
+          for (int e = 0; e < max(e0, e1); ++e) m = e < mine ? m * v[d] : m;
+        }
+        ch.mono[ql][(k + ql) & 31] = m;
+      }
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (int i = 0; i < kLdsChunk / 2; ++i) {
+      const int qi = 2 * i + (lane >> 5);
+      const float4 r0 = *reinterpret_cast<const float4*>(&ch.rot[qi][0]);
+      const float4 r1 = *reinterpret_cast<const float4*>(&ch.rot[qi][4]);
+      const float r8 = ch.rot[qi][8];
+      // source point R^T p relative to the centre, its cell and the weights
+      const float sx = r0.x * px + r0.w * py + r1.z * pz;
+      const float sy = r0.y * px + r1.x * py + r1.w * pz;
+      const float sz = r0.z * px + r1.y * py + r8 * pz;
+      const float fx = floorf(sx), fy = floorf(sy), fz = floorf(sz);
+      const float tx = sx - fx, ty = sy - fy, tz = sz - fz;
+      const int ix = (int)fx, iy = (int)fy, iz = (int)fz;
+      float val = 0.0f;
+#pragma unroll
+      for (int dz = 0; dz < 2; ++dz) {
+        const int2 s = slice[min(max(iz + dz, -R - 1), R + 1) + R + 1];
+        const int h1 = s.y + 1, pitch = 2 * s.y + 5;
+        const int x = min(max(ix, -h1 - 1), h1);
+        const int ya = min(max(iy, -h1), h1), yb = min(max(iy + 1, -h1), h1);
+        const float* ra = ball + s.x + __mul24(ya, pitch) + x;
+        const float* rb = ball + s.x + __mul24(yb, pitch) + x;
+        const float va = (1.0f - tx) * ra[0] + tx * ra[1], vb = (1.0f - tx) * rb[0] + tx * rb[1];
+        val += (dz ? tz : 1.0f - tz) * ((1.0f - ty) * va + ty * vb);
+      }
+      sum = __builtin_amdgcn_mfma_f32_32x32x2f32(ch.mono[qi][(lane + qi) & 31], val, sum, 0, 0, 0);
+    }
+    held += kLdsChunk;
+    if (held == kQChunk || st + 1 == steps) {
+      held = 0;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        acc[i] += (double)sum[i];
+        sum[i] = 0.0f;
+      }
+    }
+  }
+  __syncthreads();   // the ball is done with
+  double* red = reinterpret_cast<double*>(ball);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) red[(wave * 16 + i) * 64 + lane] = acc[i];
+  __syncthreads();
+  const size_t n = (size_t)L * L * L;
+  const double inv = 1.0 / (double)nq;
+  for (int e = tid; e < kLdsGroups * 16 * 64; e += NT) {
+    // voxel group v; element i of lane l: component 8 (i / 4) + 4 (l / 32) + i % 4, voxel l % 32
+    const int l = e & 63, i = (e >> 6) & 15, v = e >> 10;
+    const int k = 8 * (i >> 2) + 4 * (l >> 5) + (i & 3), p = vox[v * kBuildVox + (l & 31)];
+    double s = 0.0;
+    for (int q = 0; q < kLdsGroups; ++q) s += red[((q * kLdsGroups + v) * 16 + i) * 64 + l];
     if (k < na && p >= 0) T[(size_t)(a0 + k) * n + p] = (float)(s * inv);
   }
 }
@@ -826,8 +1052,8 @@ size_t ttm_workspace_size(const ttm_desc* desc, int op, int fft_n, int nz, int n
       if (nz < 1) return 0;
       return align256(mlp_train_workspace(nz));
     case TTM_OP_REFINE:
-      if (nz < 1 || ny < 0 || ny > max_refine_radius()) return 0;
-      return refine_workspace(K, nz, (float)ny);
+      if (nz < 1 || ny < 0 || ny > max_refine_radius() || desc->L < 1 || desc->L > 64) return 0;
+      return refine_workspace(K, desc->L, nz, (float)ny);
     case TTM_OP_TENSOR_WEDGE:
       if (desc->L < 1 || desc->L > 512) return 0;
       return wedge_workspace(desc->L, K);
@@ -852,8 +1078,7 @@ int ttm_build_tensor(ttm_ctx* ctx, const ttm_desc* desc, const float* tmpl, cons
   hipStream_t s = static_cast<hipStream_t>(stream);
   TTM_HIP(hipSetDevice(ctx->device));
   const int L = desc->L, K = ncomp(desc->degree, desc->dprime);
-  hipLaunchKernelGGL(k_template_norm, dim3(1), dim3(1024), 0, s, tmpl, L, desc->mask_radius,
-                     desc->filter_a, tn_out);
+  template_norm(desc, tmpl, tn_out, s);
   Exponents ex;
   exponents(desc->degree, desc->dprime, ex);
   float ax = desc->axis[0], ay = desc->axis[1], az = desc->axis[2];
@@ -869,13 +1094,24 @@ int ttm_build_tensor(ttm_ctx* ctx, const ttm_desc* desc, const float* tmpl, cons
   const int lim2 = reach_sq(desc->mask_radius);
   int reach = 0, x0;
   for (int i = 0; i < L * L; ++i) reach += row_reach(lim2, L, i / L, i % L, x0);
-  const dim3 grid((reach + kBuildVox - 1) / kBuildVox), block(64 * kBuildWaves);
-  // two tiles share a sample where more than 32 components are left
-  for (int a0 = 0; a0 < K;) {
-    const int na = std::min(2 * kCompBlock, K - a0);
-    hipLaunchKernelGGL(na > kCompBlock ? k_build<2> : k_build<1>, grid, block, 0, s, tn_out, L, lim2, quats,
-                       nq, desc->dprime, ax, ay, az, a0, na, ex, T_out);
-    a0 += na;
+  const int R = (int)std::floor(desc->mask_radius);
+  int floats = 0;
+  for (int z = -R - 1; z <= R + 1; ++z) floats += slice_floats(slice_half(desc->mask_radius, z));
+  if (floats <= kBuildBall && 2 * R + 3 <= kBuildSlices) {
+    const int vg = kLdsGroups * kBuildVox;
+    for (int a0 = 0; a0 < K; a0 += kCompBlock)
+      hipLaunchKernelGGL(k_build_lds, dim3((reach + vg - 1) / vg), dim3(64 * kLdsWaves), 0, s, tn_out, L,
+                         desc->mask_radius, lim2, quats, nq, desc->dprime, ax, ay, az, a0,
+                         std::min(kCompBlock, K - a0), ex, T_out);
+  } else {
+    const dim3 grid((reach + kBuildVox - 1) / kBuildVox), block(64 * kBuildWaves);
+    // two tiles share a sample where more than 32 components are left
+    for (int a0 = 0; a0 < K;) {
+      const int na = std::min(2 * kCompBlock, K - a0);
+      hipLaunchKernelGGL(na > kCompBlock ? k_build<2> : k_build<1>, grid, block, 0, s, tn_out, L, lim2, quats,
+                         nq, desc->dprime, ax, ay, az, a0, na, ex, T_out);
+      a0 += na;
+    }
   }
   TTM_HIP(hipGetLastError());
   return TTM_OK;
@@ -911,8 +1147,7 @@ int ttm_build_tensor_wedge(ttm_ctx* ctx, const ttm_desc* desc, const float* tmpl
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
   TTM_HIP(hipSetDevice(ctx->device));
-  hipLaunchKernelGGL(k_template_norm, dim3(1), dim3(1024), 0, s, tmpl, L, desc->mask_radius,
-                     desc->filter_a, tn_out);
+  template_norm(desc, tmpl, tn_out, s);
   const int P = wedge_box(L), B = wedge_batch(P);
   const size_t nbox = (size_t)P * P * P, nspec = spec_elems(P), n = (size_t)L * L * L;
   char* p = static_cast<char*>(ws);
@@ -1417,7 +1652,7 @@ int ttm_refine(ttm_ctx* ctx, const ttm_desc* desc, const float* g, const float* 
     return TTM_EINVAL;
   }
   const int K = ncomp(desc->degree, 4);
-  const size_t need = refine_workspace(K, n_peaks, r_s);
+  const size_t need = refine_workspace(K, desc->L, n_peaks, r_s);
   if (ws_bytes < need) {
     set_error("ttm_refine: workspace %zu < %zu", ws_bytes, need);
     return TTM_EWORKSPACE;

@@ -135,7 +135,7 @@ int launch_extract4(int degree, const ExtractArgs& a, hipStream_t s);
 // (opts supplies the multistart options of the d' = 4 orientation).
 int sphere_count(float rs);
 int max_refine_radius();
-size_t refine_workspace(int K, int n_peaks, float rs);
+size_t refine_workspace(int K, int L, int n_peaks, float rs);
 int refine(int degree, int K, const float* g, const float* w, int nz, int ny, int nx, const float* T,
            const float* tn, int L, float r, const int32_t* peaks, int n_peaks, float rs,
            const ExtractArgs& opts, int32_t* pos_out, float* quat_out, float* lncc_out,

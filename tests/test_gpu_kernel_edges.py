@@ -88,7 +88,10 @@ def _tensor_template(tn, quats, n, d, L):
     (7, 3.4, 0, 3, 1),       # one component, one rotation; the ball meets the box's faces
     (12, 5.9, 6, 3, 65),     # a second chunk of one rotation
     (9, 4.0, 4, 4, 300),     # 35 components: two tiles of 32, chunks on every wavefront
-    (8, 3.5, 8, 4, 70),      # 165 components: three launches
+    (8, 3.5, 8, 4, 70),      # 165 components: a launch per 32
+    (37, 17.0, 2, 3, 5),     # the largest ball that t' is kept in LDS for
+    (39, 19.4, 4, 4, 67),    # t' read from memory: 35 components, two tiles at once
+    (64, 31.9, 2, 3, 2),     # the largest template
 ])
 def test_tensor_template_edges(T, ctx, L, r, n, dprime, nq):
     """build_tensor against Alg. 1 in 64 bits on its own t': 1e-5 normwise, as the parity test."""
