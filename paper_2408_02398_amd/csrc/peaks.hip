@@ -3,26 +3,30 @@
 // The rule (Sec. 3.4): visit voxels by descending score, ties by ascending
 // linear index, keep a voxel when every kept peak is at least D away, stop
 // at P.  A voxel's fate depends only on higher-ranked voxels, so the first P
-// kept peaks are decided by the voxels ranked above the P-th of them.  The
-// search therefore runs on the top-ranked candidates only:
-//   1. 16-bit histogram of the score bit patterns (scores are >= 0, so the
-//      bit pattern is monotone in the value),
-//   2. the host picks the histogram bin above which at least `want`
-//      candidates lie and the kernels compact them as 64-bit keys
-//      (~score_bits << 32 | linear index), so ascending key order is exactly
-//      the visiting order,
-//   3. LSD radix sort of the keys (8-bit digits, stable ranks from wavefront
-//      ballots),
-//   4. one workgroup walks the sorted keys in chunks of 1024: every lane
-//      tests its candidate against the kept peaks through a spatial hash of
-//      cell size D; the survivors, compacted in rank order, are settled 64 at
-//      a time by one wavefront (pairwise conflict bitmasks, then a 64-step
-//      in-order acceptance on those masks).
-// If fewer than P peaks are found while lower-ranked voxels remain, the host
-// doubles `want` and repeats.
+// kept peaks are decided by the voxels ranked above the P-th of them, and any
+// threshold that leaves P kept peaks above it gives the answer.  The search with
+// a host count therefore runs on the top-ranked candidates only:
+//   1. a histogram of the score bit patterns (scores are >= 0, so the bit
+//      pattern is monotone in the value) over a sample of the map, in two
+//      levels, picks a threshold that about `want` voxels pass,
+//   2. the voxels that pass are compacted as 64-bit keys (~score_bits << 32 |
+//      linear index), so ascending key order is exactly the visiting order,
+//   3. the candidates settle in parallel (k_settle): one is kept once every
+//      higher-ranked candidate within D is dropped, and dropped once one of them
+//      is kept -- the sequential walk's answer,
+//   4. the kept ones are ranked among each other and the first P written.
+// If fewer than P peaks are found while lower-ranked voxels remain, `want` is
+// raised and the search repeats.  Too many or too dense candidates for step 3, and the
+// search whose count stays on the device, take a sorted walk instead:
+//   * LSD radix sort of the keys (8-bit digits, stable ranks from wavefront
+//     ballots),
+//   * one workgroup walks the sorted keys in chunks of 1024: every lane
+//     tests its candidate against the kept peaks through a spatial hash of
+//     cell size D; the survivors, compacted in rank order, are settled 64 at
+//     a time by one wavefront (pairwise conflict bitmasks, then a 64-step
+//     in-order acceptance on those masks).
+#include <algorithm>
 #include <climits>
-#include <cstring>
-#include <vector>
 
 #include "internal.hpp"
 
@@ -52,10 +56,27 @@ struct Region {
 // level 1: bits [19:8] of the voxels whose bits [31:20] equal `top`.
 // Each workgroup covers kHistRows rows (y) of one z slice, in groups of 8, so
 // clearing and flushing its 16 KB of bins is spread over enough voxels.
+// Of the (slice, row block) pairs one in `sample` is read.
 constexpr int kHistRows = 32;
+
+// What the threshold search leaves on the device.
+struct Pick {
+  unsigned top;       // coarse bin
+  unsigned above;     // sampled voxels in the bins over it
+  unsigned key_lo;    // candidates: score bits >= key_lo
+  unsigned count;     // candidates
+  unsigned undecided, kept;
+  int n_found;
+  unsigned pad;
+  unsigned long long pairs;   // (candidate, neighbour) pairs the settling may look at
+};
+
 __global__ __launch_bounds__(256) void k_hist(const float* __restrict__ score, Region r, int level,
-                                              unsigned top, unsigned* __restrict__ hist) {
+                                              const Pick* __restrict__ pick, int sample,
+                                              unsigned* __restrict__ hist) {
   __shared__ unsigned h[kHistBins];
+  if ((blockIdx.y + 5 * blockIdx.z) % sample) return;   // another row block in each slice
+  const unsigned top = level ? pick->top : 0u;
   for (int i = threadIdx.x; i < kHistBins; i += 256) h[i] = 0;
   __syncthreads();
   const int z = r.z0 + blockIdx.z;
@@ -99,41 +120,113 @@ __global__ __launch_bounds__(256) void k_hist(const float* __restrict__ score, R
     if (h[i]) atomicAdd(&hist[i], h[i]);
 }
 
-// Keys of the voxels whose score bits are >= key_lo, in any order (they are
-// sorted next).  A workgroup takes kCompactRows rows of one z slice and 1024
-// columns of each, 4 loads per thread in flight; a wavefront reserves the
-// slots of all its keys with one atomic.
-constexpr int kCompactRows = 4;
+// One workgroup: the bin in which the histogram, summed from the top, reaches
+// `want` sampled voxels.  Level 0 leaves the coarse bin and the sum over it, level 1
+// the threshold (key_lo stays 0, every voxel, when all bins together stay below
+// `want`).
+__global__ __launch_bounds__(1024) void k_pick(const unsigned* __restrict__ hist, int level, unsigned want, Pick* pick) {
+  __shared__ unsigned sum[1024];
+  const int t = threadIdx.x;
+  unsigned v[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = hist[kHistBins - 1 - (4 * t + i)];   // from the top down
+  const unsigned own = (v[0] + v[1]) + (v[2] + v[3]);
+  sum[t] = own;
+  __syncthreads();
+  for (int off = 1; off < 1024; off <<= 1) {
+    const unsigned o = t >= off ? sum[t - off] : 0u;
+    __syncthreads();
+    sum[t] += o;
+    __syncthreads();
+  }
+  const unsigned base = level ? pick->above : 0u, top = level ? pick->top : 0u;
+  const bool none = level && top == 0xFFFFFFFFu;
+  __syncthreads();
+  unsigned run = base + sum[t] - own;
+  if (t == 0 && level == 0 && sum[1023] < want) pick->top = 0xFFFFFFFFu;   // key_lo stays 0
+  if (none || run >= want) return;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (run < want && run + v[i] >= want) {
+      const unsigned bin = kHistBins - 1 - (4 * t + i);
+      if (level == 0) {
+        pick->top = bin;
+        pick->above = run;
+      } else {
+        pick->key_lo = top << 20 | bin << 8;
+      }
+    }
+    run += v[i];
+  }
+}
+
+// Keys of the voxels whose score bits are >= key_lo, in any order.  A workgroup
+// takes kCompactRows rows of one z slice in pieces of 256 columns, a wavefront four
+// pieces at a time, its 16 loads in flight.  The keys gather in LDS (those past
+// kCompactList go out by themselves), so a workgroup reserves its slots with one
+// atomic: the counter is one address for the whole chip, and an atomic for each 64
+// voxels with a key in them bound this at 465 us for 131 000 keys of
+// 512 x 512 x 928 (now 280 us, the map read once).
+constexpr int kCompactRows = 16, kCompactList = 1024;
 __global__ __launch_bounds__(256) void k_compact(const float* __restrict__ score, Region r,
-                                                 unsigned key_lo,
+                                                 const unsigned* __restrict__ key_lo_at,
                                                  unsigned long long* __restrict__ keys,
                                                  unsigned* __restrict__ counter) {
+  __shared__ unsigned long long list[kCompactList];
+  __shared__ unsigned n_list, slot;
+  constexpr int PB = 4;   // pieces whose loads are in flight together
+  const unsigned key_lo = key_lo_at ? *key_lo_at : 0u;
   const int z = r.z0 + blockIdx.z, y0 = r.y0 + blockIdx.y * kCompactRows;
-  const int xb = r.x0 + blockIdx.x * 1024 + threadIdx.x;
-  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const unsigned long long lt = (1ull << lane) - 1ull;
-  const int nrows = min(kCompactRows, r.y1 - y0 + 1);
-  for (int yy = 0; yy < nrows; ++yy) {
-    const size_t row = ((size_t)z * r.ny + y0 + yy) * r.nx;
-    float v[4];
+  const int nch = (r.x1 - r.x0 + 256) / 256;
+  const int items = min(kCompactRows, r.y1 - y0 + 1) * nch;
+  if (threadIdx.x == 0) n_list = 0;
+  __syncthreads();
+  for (int it = wave; it < items; it += 4 * PB) {
+    float v[PB][4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = xb + 256 * k <= r.x1 ? score[row + xb + 256 * k] : 0.0f;
+    for (int i = 0; i < PB; ++i) {
+      const int c = min(it + 4 * i, items - 1), yy = c / nch;
+      const size_t row = ((size_t)z * r.ny + y0 + yy) * r.nx;
+      const int xb = r.x0 + (c - yy * nch) * 256 + lane;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int x = xb + 256 * k;
-      const unsigned bits = score_bits(v[k]);
-      const bool take = x <= r.x1 && bits >= key_lo;
-      const unsigned long long bal = __ballot(take);
-      if (bal == 0ull) continue;  // uniform across the wavefront
-      const int leader = __ffsll((long long)bal) - 1;
-      unsigned base = 0;
-      if (lane == leader) base = atomicAdd(counter, (unsigned)__popcll(bal));
-      base = (unsigned)__shfl((int)base, leader);
-      if (take)
-        keys[base + __popcll(bal & lt)] = ((unsigned long long)(~bits) << 32) |
-                                          (unsigned long long)(row + x);
+      for (int k = 0; k < 4; ++k) v[i][k] = score[row + min(xb + 64 * k, r.x1)];
+    }
+#pragma unroll
+    for (int i = 0; i < PB; ++i) {
+      const int c = it + 4 * i, yy = c / nch;
+      if (c >= items) break;  // uniform
+      const size_t row = ((size_t)z * r.ny + y0 + yy) * r.nx;
+      const int xb = r.x0 + (c - yy * nch) * 256 + lane;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int x = xb + 64 * k;
+        const unsigned bits = score_bits(v[i][k]);
+        const bool take = x <= r.x1 && bits >= key_lo;
+        const unsigned long long bal = __ballot(take);
+        if (bal == 0ull) continue;  // uniform across the wavefront
+        const unsigned long long key = ((unsigned long long)(~bits) << 32) |
+                                       (unsigned long long)(row + x);
+        unsigned at = 0;
+        if (lane == 0) at = atomicAdd(&n_list, (unsigned)__popcll(bal));
+        at = (unsigned)__shfl((int)at, 0) + __popcll(bal & lt);
+        if (take && at < kCompactList) list[at] = key;
+        const unsigned long long over = __ballot(take && at >= kCompactList);
+        if (over == 0ull) continue;
+        unsigned base = 0;
+        if (lane == 0) base = atomicAdd(counter, (unsigned)__popcll(over));
+        base = (unsigned)__shfl((int)base, 0);
+        if (take && at >= kCompactList) keys[base + __popcll(over & lt)] = key;
+      }
     }
   }
+  __syncthreads();
+  const unsigned n = min(n_list, (unsigned)kCompactList);
+  if (n == 0) return;  // uniform
+  if (threadIdx.x == 0) slot = atomicAdd(counter, n);
+  __syncthreads();
+  for (unsigned i = threadIdx.x; i < n; i += 256) keys[slot + i] = list[i];
 }
 
 __global__ void k_fill(unsigned long long* __restrict__ keys, size_t from, size_t to) {
@@ -234,6 +327,172 @@ __global__ __launch_bounds__(kSortBlock) void k_rs_scatter(
     for (int w = 0; w < NW; ++w) tot += wcnt[w][tid];
     run[tid] += tot;
     __syncthreads();
+  }
+}
+
+// ---------------------------------------------------------------- settling
+// Candidates in the order of the exclusion grid's cells (edge >= D): those within
+// D of one lie in the 27 cells around its own, which are nine runs of the list.
+// A short list (up to kFlatMax) is one cell.
+constexpr unsigned kSettleMax = 1u << 20;   // candidates
+constexpr unsigned kFlatMax = 4096;
+constexpr unsigned kKeptMax = 16384;        // kept ones
+constexpr int kSettleRounds = 6;            // between two looks at what is left (random maps take about 11)
+constexpr int kSettleLooks = 32;            // then the sorted walk
+// Pairs up to which the candidates settle in parallel.  Where candidates fill the
+// map (a peak count out of reach makes every voxel one) each would look at every
+// voxel of 27 cells; the sorted walk tests a key against the few kept peaks of
+// those cells instead.
+constexpr unsigned long long kSettlePairs = 1ull << 29;
+
+struct Settle {
+  const unsigned long long* in;   // keys as compacted
+  unsigned long long* key;        // in cell order
+  ushort4* pos;                   // z, y, x
+  int* state;                     // 0 undecided, 1 kept, 2 dropped
+  unsigned* start;                // first candidate of each cell, ncell + 1
+  unsigned* fill;                 // candidates placed per cell
+  unsigned m;
+  int flat;
+  int ny, nx;
+  float d2, cell;
+  int gz, gy, gx;
+  Pick* pick;
+  unsigned long long* kept;       // kKeptMax keys
+};
+
+__device__ __forceinline__ ushort4 key_pos(unsigned long long key, int ny, int nx) {
+  const unsigned lin = (unsigned)(key & 0xffffffffull), yx = (unsigned)ny * (unsigned)nx;
+  const unsigned z = lin / yx, rz = lin - z * yx, y = rz / (unsigned)nx;
+  return make_ushort4((unsigned short)z, (unsigned short)y, (unsigned short)(rz - y * (unsigned)nx), 0);
+}
+__device__ __forceinline__ int cell_of(const Settle& s, const ushort4& p) {
+  return ((int)(p.x / s.cell) * s.gy + (int)(p.y / s.cell)) * s.gx + (int)(p.z / s.cell);
+}
+
+// Candidates per cell (cleared before), then, with the cells' starts known, the
+// candidates in cell order (in any order within a cell).
+template <bool SCATTER>
+__global__ __launch_bounds__(256) void k_cells(Settle s) {
+  const unsigned i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= s.m) return;
+  const unsigned long long key = s.in[i];
+  const ushort4 p = key_pos(key, s.ny, s.nx);
+  if (!SCATTER) {
+    atomicAdd(&s.start[cell_of(s, p)], 1u);
+  } else {
+    unsigned at = i;
+    if (!s.flat) {
+      const int c = cell_of(s, p);
+      at = s.start[c] + atomicAdd(&s.fill[c], 1u);
+    }
+    s.key[at] = key;
+    s.pos[at] = p;
+    s.state[at] = 0;
+  }
+}
+
+// Pairs of the list: each cell's candidates times those of its 27 cells.
+__global__ __launch_bounds__(256) void k_pairs(Settle s) {
+  const int c = blockIdx.x * 256 + threadIdx.x;
+  unsigned long long v = 0;
+  if (c < s.gz * s.gy * s.gx) {
+    const int x = c % s.gx, y = (c / s.gx) % s.gy, z = c / (s.gx * s.gy);
+    for (int o = 0; o < 9; ++o) {
+      const int z2 = z + o / 3 - 1, y2 = y + o % 3 - 1;
+      if (z2 < 0 || z2 >= s.gz || y2 < 0 || y2 >= s.gy) continue;
+      const int row = (z2 * s.gy + y2) * s.gx;
+      v += s.start[row + min(x + 1, s.gx - 1) + 1] - s.start[row + max(x - 1, 0)];
+    }
+    v *= s.start[c + 1] - s.start[c];
+  }
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off);
+  if ((threadIdx.x & 63) == 0 && v) atomicAdd(&s.pick->pairs, v);
+}
+
+// One round, a wavefront per undecided candidate: among the higher-ranked
+// candidates within D, a kept one drops it, else an undecided one makes it wait
+// for a later round, else it is kept.  States only ever leave 0, so one read too
+// early costs a round and nothing else.  A walk in rank order by one workgroup
+// spent 2.4 ms on 131 000 candidates of 2000 peaks; all rounds of this take 0.34 ms.
+__global__ __launch_bounds__(256) void k_settle(Settle s) {
+  const unsigned i = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const unsigned lane = threadIdx.x & 63;
+  if (i >= s.m || s.pick->pairs > kSettlePairs || s.state[i] != 0) return;   // uniform per wavefront
+  const unsigned long long key = s.key[i];
+  const ushort4 p = s.pos[i];
+  const int hz = (int)(p.x / s.cell), hy = (int)(p.y / s.cell), hx = (int)(p.z / s.cell);
+  bool wait = false;
+  for (int o = 0; o < (s.flat ? 1 : 9); ++o) {
+    unsigned b = 0, e = s.m;
+    if (!s.flat) {
+      const int z2 = hz + o / 3 - 1, y2 = hy + o % 3 - 1;
+      if (z2 < 0 || z2 >= s.gz || y2 < 0 || y2 >= s.gy) continue;
+      const int row = (z2 * s.gy + y2) * s.gx;
+      b = s.start[row + max(hx - 1, 0)];
+      e = s.start[row + min(hx + 1, s.gx - 1) + 1];
+    }
+    for (unsigned j0 = b; j0 < e; j0 += 64) {
+      const unsigned j = j0 + lane;
+      int st = 2;
+      if (j < e && s.key[j] < key) {
+        const ushort4 q = s.pos[j];
+        const float ddz = (float)((int)p.x - (int)q.x), ddy = (float)((int)p.y - (int)q.y),
+                    ddx = (float)((int)p.z - (int)q.z);
+        if (ddz * ddz + ddy * ddy + ddx * ddx < s.d2)
+          st = __hip_atomic_load(&s.state[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      if (__ballot(st == 1)) {
+        if (lane == 0) __hip_atomic_store(&s.state[i], 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+      }
+      wait = wait || __ballot(st == 0) != 0ull;
+    }
+  }
+  if (!wait && lane == 0) __hip_atomic_store(&s.state[i], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Undecided candidates counted, kept ones gathered (the counters cleared before);
+// more than kKeptMax kept ones stand for a list that is not settled here.
+__global__ __launch_bounds__(256) void k_gather(Settle s) {
+  const unsigned i = blockIdx.x * 256 + threadIdx.x;
+  if (s.pick->pairs > kSettlePairs) {   // uniform
+    if (i == 0) s.pick->kept = kKeptMax + 1;
+    return;
+  }
+  const int st = i < s.m ? s.state[i] : 2;
+  const unsigned long long wait = __ballot(st == 0), keep = __ballot(st == 1);
+  const int lane = threadIdx.x & 63;
+  if (lane == 0 && wait) atomicAdd(&s.pick->undecided, (unsigned)__popcll(wait));
+  if (keep == 0ull) return;
+  unsigned base = 0;
+  if (lane == 0) base = atomicAdd(&s.pick->kept, (unsigned)__popcll(keep));
+  base = (unsigned)__shfl((int)base, 0) + __popcll(keep & ((1ull << lane) - 1ull));
+  if (st == 1 && base < kKeptMax) s.kept[base] = s.key[i];
+}
+
+// Rank of each kept key among the kept, and its place in the output.
+__global__ __launch_bounds__(256) void k_rank(const unsigned long long* __restrict__ kept, Pick* pick, int ny, int nx,
+                                              int top_p, int* __restrict__ peaks, float* __restrict__ vals) {
+  __shared__ unsigned long long tile[1024];
+  const unsigned n = pick->kept, i = blockIdx.x * 256 + threadIdx.x;
+  if (n > kKeptMax || blockIdx.x * 256 >= n) return;   // uniform
+  if (i == 0) pick->n_found = (int)min(n, (unsigned)top_p);
+  const unsigned long long key = i < n ? kept[i] : ~0ull;
+  int rank = 0;
+  for (unsigned t0 = 0; t0 < n; t0 += 1024) {
+    __syncthreads();
+    for (unsigned k = threadIdx.x; k < 1024; k += 256) tile[k] = t0 + k < n ? kept[t0 + k] : ~0ull;
+    __syncthreads();
+#pragma unroll 8
+    for (int k = 0; k < 1024; ++k) rank += tile[k] < key ? 1 : 0;
+  }
+  if (i < n && rank < top_p) {
+    const ushort4 p = key_pos(key, ny, nx);
+    peaks[3 * rank + 0] = p.x;
+    peaks[3 * rank + 1] = p.y;
+    peaks[3 * rank + 2] = p.z;
+    vals[rank] = __uint_as_float(~(unsigned)(key >> 32));
   }
 }
 
@@ -617,7 +876,14 @@ size_t peaks_head_bytes(int64_t n_voxels) {
   const size_t b = 2 * cand * 8 + kHistBins * 4 + 256 * nblk * 4 + 256 + 1024;
   return (b + 255) / 256 * 256;
 }
-constexpr size_t kPeaksTailBytes = kHashShorts * 2 + 256;
+constexpr size_t kPeaksTailBytes = (kHashShorts * 2 + 256 + 255) / 256 * 256;
+
+// The settling's arrays behind the tail: positions and states of at most
+// kSettleMax candidates, the cells' starts and fills, the kept keys.
+size_t settle_bytes(int64_t n_voxels) {
+  const size_t m = ((size_t)std::min<int64_t>(n_voxels, kSettleMax) + 1) / 2 * 2;
+  return m * 12 + (2 * kMaxCells + 64) * 4 + (size_t)kKeptMax * 8 + 1024;
+}
 
 // The greedy walk over m sorted keys in `srt` (`spare` holds as many):
 // `rounds` times a walk over the first kWalkKeys keys of the list and the
@@ -683,13 +949,13 @@ int find_peaks_async(const float* score, int nz, int ny, int nx, const int32_t l
   unsigned* hist = reinterpret_cast<unsigned*>(keys_b + cand_cap);
   unsigned* counter = hist + kHistBins;
   unsigned* shist = reinterpret_cast<unsigned*>(counter + 128);
-  const dim3 cgrid((hi[2] - lo[2] + 1 + 1023) / 1024, (hi[1] - lo[1] + kCompactRows) / kCompactRows,
+  const dim3 cgrid(1, (hi[1] - lo[1] + kCompactRows) / kCompactRows,
                    hi[0] - lo[0] + 1);
   const size_t m = (size_t)nvalid;
   const size_t mpad = (m + kSortTile - 1) / kSortTile * kSortTile;
   const int nblk = (int)(mpad / kSortTile);
   fill_zero(counter, 4, s);
-  hipLaunchKernelGGL(k_compact, cgrid, dim3(256), 0, s, score, r, 0u, keys_a, counter);
+  hipLaunchKernelGGL(k_compact, cgrid, dim3(256), 0, s, score, r, nullptr, keys_a, counter);
   if (mpad > m) {
     hipLaunchKernelGGL(k_fill, dim3((unsigned)((mpad - m + 255) / 256)), dim3(256), 0, s, keys_a, m,
                        mpad);
@@ -711,7 +977,7 @@ int find_peaks_async(const float* score, int nz, int ny, int nx, const int32_t l
 }
 
 size_t peaks_workspace(int64_t n_voxels) {
-  return peaks_head_bytes(n_voxels) + kPeaksTailBytes;
+  return peaks_head_bytes(n_voxels) + kPeaksTailBytes + settle_bytes(n_voxels);
 }
 
 int find_peaks(const float* score, int nz, int ny, int nx, const int32_t lo[3],
@@ -741,54 +1007,83 @@ int find_peaks(const float* score, int nz, int ny, int nx, const int32_t lo[3],
   int* nfound_dev = reinterpret_cast<int*>(counter + 64);
   unsigned* shist = reinterpret_cast<unsigned*>(nfound_dev + 64);
 
-  const dim3 cgrid((hi[2] - lo[2] + 1 + 1023) / 1024, (hi[1] - lo[1] + kCompactRows) / kCompactRows,
+  const dim3 cgrid(1, (hi[1] - lo[1] + kCompactRows) / kCompactRows,
                    hi[0] - lo[0] + 1);
   const dim3 hgrid(1, (hi[1] - lo[1] + kHistRows) / kHistRows, hi[0] - lo[0] + 1);
-  std::vector<unsigned> h0(kHistBins), h1(kHistBins);
-  fill_zero(hist, kHistBins * 4, s);
-  hipLaunchKernelGGL(k_hist, hgrid, dim3(256), 0, s, score, r, 0, 0u, hist);
-  TTM_HIP(hipMemcpyAsync(h0.data(), hist, kHistBins * 4, hipMemcpyDeviceToHost, s));
-  TTM_HIP(hipStreamSynchronize(s));
-  int top_cached = -1;
+  char* tail = w + peaks_head_bytes(nvalid) + kPeaksTailBytes;
+  const size_t sm = ((size_t)std::min<int64_t>(nvalid, kSettleMax) + 1) / 2 * 2;
+  Settle st;
+  st.in = keys_a;
+  st.key = keys_b;
+  st.pos = reinterpret_cast<ushort4*>(tail);
+  st.state = reinterpret_cast<int*>(tail + sm * 8);
+  st.kept = reinterpret_cast<unsigned long long*>(tail + sm * 12);
+  st.start = reinterpret_cast<unsigned*>(st.kept + kKeptMax);
+  const int ncell = gz * gy * gx;
+  st.fill = st.start + ncell + 1;
+  Pick* pick = reinterpret_cast<Pick*>(st.start + 2 * kMaxCells + 64);
+  st.pick = pick;
+  st.ny = ny;
+  st.nx = nx;
+  st.cell = cell;
+  st.d2 = min_dist * min_dist;
+  st.gz = gz;
+  st.gy = gy;
+  st.gx = gx;
 
-  int64_t want = std::max<int64_t>(64 * (int64_t)top_p, 1 << 16);
-  while (true) {
-    // coarse bin (bits 31:20) such that it and the bins above hold >= want voxels
-    int64_t above = 0;
-    int b0 = kHistBins - 1;
-    for (; b0 >= 0; --b0) {
-      if (above + h0[b0] >= want) break;
-      above += h0[b0];
-    }
-    unsigned key_lo = 0;
-    int64_t acc = 0;
-    if (b0 < 0) {
-      key_lo = 0;             // every voxel
-      acc = above;
-    } else {
-      if (top_cached != b0) {
+  // The threshold comes from a sample of at least 4 million voxels (every 16th
+  // (slice, row block) pair of a large map): it only sets how many candidates
+  // there are, not the answer.
+  const int sample = (int)std::min<int64_t>(16, std::max<int64_t>(1, nvalid >> 22));
+  Pick got;
+  for (int64_t want = std::max<int64_t>(64 * (int64_t)top_p, kFlatMax);; want *= 4) {
+    fill_zero(pick, sizeof(Pick), s);
+    if (want < nvalid) {
+      const unsigned want_s = (unsigned)std::max<int64_t>(1, want / sample);
+      for (int level = 0; level < 2; ++level) {
         fill_zero(hist, kHistBins * 4, s);
-        hipLaunchKernelGGL(k_hist, hgrid, dim3(256), 0, s, score, r, 1, (unsigned)b0, hist);
-        TTM_HIP(hipMemcpyAsync(h1.data(), hist, kHistBins * 4, hipMemcpyDeviceToHost, s));
-        TTM_HIP(hipStreamSynchronize(s));
-        top_cached = b0;
+        hipLaunchKernelGGL(k_hist, hgrid, dim3(256), 0, s, score, r, level, pick, sample, hist);
+        hipLaunchKernelGGL(k_pick, dim3(1), dim3(1024), 0, s, hist, level, want_s, pick);
       }
-      int64_t in = 0;
-      int b1 = kHistBins - 1;
-      for (; b1 > 0; --b1) {
-        if (above + in + h1[b1] >= want) break;
-        in += h1[b1];
-      }
-      in += h1[b1];
-      key_lo = ((unsigned)b0 << 20) | ((unsigned)b1 << 8);
-      acc = above + in;
     }
-    const bool all = (acc >= nvalid) || key_lo == 0;
-    const int64_t m = acc;
+    hipLaunchKernelGGL(k_compact, cgrid, dim3(256), 0, s, score, r, &pick->key_lo, keys_a, &pick->count);
+    TTM_HIP(hipMemcpyAsync(&got, pick, sizeof(Pick), hipMemcpyDeviceToHost, s));
+    TTM_HIP(hipStreamSynchronize(s));
+    const int64_t m = got.count;
+    const bool all = m >= nvalid || got.key_lo == 0;
+    if (m <= (int64_t)kSettleMax) {
+      st.m = (unsigned)m;
+      const dim3 mg((unsigned)((m + 255) / 256));
+      st.flat = m <= (int64_t)kFlatMax;
+      if (!st.flat) {
+        fill_zero(st.start, (2 * (size_t)ncell + 1) * 4, s);
+        hipLaunchKernelGGL(k_cells<false>, mg, dim3(256), 0, s, st);
+        hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, st.start, ncell + 1);
+        hipLaunchKernelGGL(k_pairs, dim3((ncell + 255) / 256), dim3(256), 0, s, st);
+      }
+      if (m > 0) hipLaunchKernelGGL(k_cells<true>, mg, dim3(256), 0, s, st);
+      for (int look = 0; look == 0 || (got.undecided && got.pairs <= kSettlePairs && look < kSettleLooks); ++look) {
+        fill_zero(&pick->undecided, 8, s);
+        if (m > 0) {
+          for (int k = 0; k < kSettleRounds; ++k)
+            hipLaunchKernelGGL(k_settle, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, s, st);
+          hipLaunchKernelGGL(k_gather, mg, dim3(256), 0, s, st);
+          hipLaunchKernelGGL(k_rank, dim3(kKeptMax / 256), dim3(256), 0, s, st.kept, pick, ny, nx, top_p,
+                             peaks_out, vals_out);
+        }
+        TTM_HIP(hipMemcpyAsync(&got, pick, sizeof(Pick), hipMemcpyDeviceToHost, s));
+        TTM_HIP(hipStreamSynchronize(s));
+      }
+      if (!got.undecided && got.kept <= kKeptMax) {
+        if (got.n_found >= top_p || all) {
+          *n_found_host = got.n_found;
+          return 0;
+        }
+        continue;
+      }
+    }
     const size_t mpad = ((size_t)m + kSortTile - 1) / kSortTile * kSortTile;
     const int nblk = (int)(mpad / kSortTile);
-    fill_zero(counter, 4, s);
-    hipLaunchKernelGGL(k_compact, cgrid, dim3(256), 0, s, score, r, key_lo, keys_a, counter);
     if (mpad > (size_t)m) {
       hipLaunchKernelGGL(k_fill, dim3((unsigned)((mpad - m + 255) / 256)), dim3(256), 0, s, keys_a,
                          (size_t)m, mpad);
@@ -813,7 +1108,6 @@ int find_peaks(const float* score, int nz, int ny, int nx, const int32_t lo[3],
       *n_found_host = nf;
       return 0;
     }
-    want *= 4;
   }
 }
 

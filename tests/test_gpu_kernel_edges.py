@@ -194,3 +194,60 @@ def test_refine_field_and_lncc_edges(T, ctx, L, r, n, n_peaks, rs):
             best = max(float(orc.sym.inner_power(C, p, n)) for p in probe)
             assert float(lam) >= best - 1e-4 * float(orc.sym.frobenius(C, n, 4))
     assert np.all(lr >= lp)
+
+
+def _greedy(score, lo, hi, top, dist):
+    """Find Peaks by its definition: the first maximum of the valid box outside
+    the balls of the peaks kept so far (np.argmax takes the lowest index on ties)."""
+    m = np.full(score.shape, -1.0)
+    box = tuple(slice(a, b + 1) for a, b in zip(lo, hi))
+    s = score[box].astype(np.float64)
+    m[box] = np.where(s > 0, s, 0.0)
+    zz, yy, xx = np.ogrid[:m.shape[0], :m.shape[1], :m.shape[2]]
+    out = []
+    while len(out) < top:
+        i = int(np.argmax(m))
+        z, y, x = np.unravel_index(i, m.shape)
+        if m[z, y, x] < 0:
+            break
+        out.append((int(z), int(y), int(x)))
+        m[(zz - z) ** 2 + (yy - y) ** 2 + (xx - x) ** 2 < dist * dist] = -1.0
+        m[z, y, x] = -1.0
+    return out
+
+
+@pytest.mark.parametrize("kind,shape,top,dist", [
+    ("noise", (20, 30, 70), 40, 6.0),        # fewer voxels than candidates are wanted: every voxel settles
+    ("noise", (40, 61, 130), 2000, 3.0),     # thousands of peaks, long chains of waiting candidates
+    ("constant", (30, 40, 50), 2048, 4.0),   # ties only: the visiting order is the index order
+    ("constant", (110, 104, 103), 12, 30.0), # more tied candidates than settle in parallel: the sorted walk
+    ("ramp", (16, 20, 400), 60, 7.0),        # one chain: each candidate waits for its neighbour
+    ("flat", (33, 40, 64), 50, 5.0),         # peaks on an exact zero background, fewer than asked for above it
+    ("dense", (24, 25, 24), 2048, 0.0),      # distance 0: every voxel is a peak (the most grid cells)
+    ("blobs", (150, 200, 230), 300, 9.0),    # the threshold's two levels over a sampled map
+])
+def test_find_peaks_candidates(T, ctx, kind, shape, top, dist):
+    """find_peaks against the rule's definition, bit for bit."""
+    import torch
+    rng = np.random.default_rng(sum(shape))
+    if kind == "constant":
+        s = np.full(shape, 0.25, dtype=np.float32)
+    elif kind == "ramp":
+        s = np.broadcast_to(np.linspace(1.0, 2.0, shape[2], dtype=np.float32), shape).copy()
+    elif kind == "flat":
+        s = np.zeros(shape, dtype=np.float32)
+        s.ravel()[rng.integers(0, s.size, 30)] = rng.uniform(0.1, 1.0, 30).astype(np.float32)
+        s[5, 6, 7], s[0, 0, 0] = np.nan, -1.0
+    else:
+        s = rng.uniform(0.1, 0.2, shape).astype(np.float32)
+        if kind == "blobs":
+            k = np.exp(-(np.arange(-5, 6) ** 2) / 8.0)
+            b = (k[:, None, None] * k[None, :, None] * k[None, None, :]).astype(np.float32)
+            for _ in range(250):
+                z, y, x = (int(rng.integers(5, d - 6)) for d in shape)
+                s[z - 5:z + 6, y - 5:y + 6, x - 5:x + 6] += rng.uniform(0.2, 0.9) * b
+    lo, hi = (2, 1, 3), tuple(d - 3 for d in shape)
+    peaks, vals = T.find_peaks(ctx, torch.from_numpy(s).cuda(), lo, hi, top, dist)
+    ref = _greedy(s, lo, hi, top, dist)
+    assert peaks.cpu().numpy().tolist() == [list(p) for p in ref]
+    assert np.array_equal(vals.cpu().numpy(), np.array([max(s[p], 0.0) if s[p] == s[p] else 0.0 for p in ref], np.float32))
