@@ -42,7 +42,7 @@ namespace {
 
 constexpr int kNewtonFirst = 5;   // Newton steps from the learned start inside k_learned
 constexpr int kRefill = 8;        // a pooled wavefront refills once this many lanes wait
-constexpr int kPoolGroups = 4096; // persistent pooled grid (one wavefront per group)
+constexpr int kPoolWaves = 4;     // wavefronts of a pooled workgroup
 constexpr int kStartBlock = 16;   // starts whose run results are held at once
 
 // Workspace layout (one 256-byte aligned array each, `plane` entries):
@@ -589,6 +589,12 @@ __global__ __launch_bounds__(256) void k_prepare(ExtractArgs a, Items it, int wr
 // the chunk's next runs as soon as kRefill of them wait.  Each run ends at
 // |delta lambda| <= tol or max_iter updates; its (u, lambda) is written to
 // res[(q % R) * plane + item] (and, for cont, conv[item]).
+// Bound by vector issue: an update at degree 4 is 62 multiplies and adds of the contraction
+// and 16 of the normalisation, so what stands around them counts.  The step's
+// loop holds nothing else: an ended lane keeps its answer until the refill writes
+// it, the queue is uniform, and the refill (as many instructions as two steps, for
+// a few lanes) has neither a division nor a square root.  97^3 voxels of degree 6:
+// 4.09 -> 3.18 ms with score and polish.
 struct RunArgs {
   Items items;
   int per_item;   // R
@@ -596,24 +602,70 @@ struct RunArgs {
   unsigned long long* ctr;
 };
 
+// 1 / sqrt(n2) as rsqrtf gives it; its steps for subnormal n2 are taken only by
+// a wavefront that holds one.
+__device__ __forceinline__ float rsqrt_wave(float n2) {
+  if (__ballot(n2 < 0x1p-126f) != 0ull) return rsqrtf(n2);
+  return __builtin_amdgcn_rsqf(n2);
+}
+
+// Orders a wavefront's LDS accesses (its own reads and writes reach LDS in order).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Pooled workgroups for so many runs.  A run of max_iter updates is a serial chain,
+// and it advances at its wavefront's share of the SIMD: few runs end soonest with one
+// wavefront per SIMD (a workgroup per CU), many with all that fit.  Score and
+// orientation of e^3 voxels of degree 4 with 256 / 512 / 1024 / 2048 workgroups:
+// e = 24 (220 000 runs) 226 / 270 / 390 / 419 us, e = 32 (520 000) 322 / 291 / 419 /
+// 646, e = 48 (1.8 million) 725 / 475 / 447 / 593, e = 80 (8.2 million) 2625 / 1578 /
+// 1170 / 1110; degree 6 changes at the same counts.
+__host__ __device__ inline unsigned pool_groups(size_t runs) {
+  return runs < 350000 ? 256 : runs < 1000000 ? 512 : runs < 4000000 ? 1024 : 2048;
+}
+
 template <int N, bool CONT>
-__global__ __launch_bounds__(64) void k_runs(ExtractArgs a, RunArgs r) {
+__global__ __launch_bounds__(64 * kPoolWaves) void k_runs(ExtractArgs a, RunArgs r) {
   constexpr int K = ncomp3(N);
-  __shared__ float st[64 * 3];
-  __shared__ float cs[K][64];     // chunk tensors, [component][item]
-  __shared__ float ca[64];        // shift per item
-  __shared__ float cz[64];        // ||C||_F per item (0: nothing to run)
-  __shared__ float4 cu[CONT ? 64 : 1];
-  __shared__ int ci[CONT ? 64 : 1];
-  const int lane = threadIdx.x;
-  for (int i = lane; i < a.n_starts * 3; i += 64) st[i] = a.starts[i];
-  __syncthreads();
+  constexpr int kRest = 64 / kPoolWaves;   // runs a wavefront may hand over
+  constexpr int kState = K + 9;            // words of a run
+  static_assert(kState * kRest <= K * 64, "a wavefront's runs fit its chunk's place");
+  __shared__ float st[3][kStartBlock];   // this block's starts, normalised
+  __shared__ float cs_all[kPoolWaves][K][64];   // chunk tensors, [component][item]
+  __shared__ float ca_all[kPoolWaves][64];      // shift per item
+  __shared__ float cz_all[kPoolWaves][64];      // ||C||_F per item (0: nothing to run)
+  __shared__ float4 cu_all[CONT ? kPoolWaves : 1][64];
+  __shared__ int ci_all[CONT ? kPoolWaves : 1][64];
+  __shared__ int n_rest[kPoolWaves];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  float (&cs)[K][64] = cs_all[wave];
+  float (&ca)[64] = ca_all[wave];
+  float (&cz)[64] = cz_all[wave];
+  float4 (&cu)[64] = cu_all[CONT ? wave : 0];
+  int (&ci)[64] = ci_all[CONT ? wave : 0];
+  const int R = r.per_item;
   const Ws w = ws_layout(a.ws, a.plane);
   const unsigned n_items = r.items.n(a);
-  const int R = r.per_item;
+  const unsigned groups = min(gridDim.x, pool_groups((size_t)n_items * R));
+  if (blockIdx.x >= groups) return;
+  if (!CONT && (int)threadIdx.x < R) {
+    const float* p = a.starts + 3 * (r.s0 + lane);
+    const float sx = p[0], sy = p[1], sz = p[2];
+    const float rs = 1.0f / sqrtf(sx * sx + sy * sy + sz * sz);
+    st[0][lane] = sx * rs; st[1][lane] = sy * rs; st[2][lane] = sz * rs;
+  }
+  __syncthreads();
+  // q / R = q * rdiv >> 20 for q < 64 R: with rdiv R = 2^20 + e, e < R <= 16, the
+  // product is off by q e / R < 2^10 < 2^20 / R
+  const unsigned rdiv = ((1u << 20) + R - 1) / R;
+  static_assert(kStartBlock <= 16, "the division above");
   // items per chunk: up to 64, fewer when the list is short, so that every
   // wavefront of the grid gets several chunks
-  const unsigned per_wave = (n_items + 4 * gridDim.x - 1) / (4 * gridDim.x);
+  const unsigned parts = 4 * kPoolWaves * groups;
+  const unsigned per_wave = (n_items + parts - 1) / parts;
   const unsigned chunk = per_wave < 1 ? 1 : (per_wave > 64 ? 64 : per_wave);
   // chunk state (uniform across the wavefront)
   unsigned chunk_base = 0;
@@ -623,126 +675,161 @@ __global__ __launch_bounds__(64) void k_runs(ExtractArgs a, RunArgs r) {
   float c[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) c[k] = 0.0f;
-  float alpha = 0.0f, ux = 0.0f, uy = 0.0f, uz = 0.0f, g0 = 0.0f, g1 = 0.0f, g2 = 0.0f, lam = 0.0f;
-  int iters = 0, s = 0;
+  float alpha = 0.0f, ux = 0.0f, uy = 0.0f, uz = 0.0f, lam = 0.0f;
+  float dlam = 0.0f;             // lambda's last change
+  int left = -1;                 // updates left of a run under way, ~left of an ended one
+  float4* out = nullptr;         // where the run's answer goes
   unsigned j = 0;
-  bool first = false, busy = false;
-  unsigned long long n_steps = 0, n_runs = 0;
-  while (true) {
-    unsigned long long waiting = __ballot(!busy);
-    int n_wait = __popcll(waiting);
-    if (n_wait == 64 && exhausted && next_q == chunk_runs) break;
-    if (n_wait >= kRefill || n_wait == 64) {
-      while (n_wait > 0) {
-        if (next_q == chunk_runs) {
-          if (exhausted) break;
-          // next chunk of items
-          unsigned long long base = 0;
-          if (lane == 0) base = atomicAdd(r.ctr, (unsigned long long)chunk);
-          base = __shfl(base, 0);
-          if (base >= n_items) {
-            exhausted = true;
-            break;
-          }
-          const int cnt = (n_items - base) < chunk ? (int)(n_items - base) : (int)chunk;
-          if (base + chunk >= n_items) exhausted = true;
-          chunk_base = (unsigned)base;
-          chunk_runs = cnt * R;
-          next_q = 0;
-          __syncthreads();   // earlier LDS reads of the previous chunk are complete
-          if (lane < cnt) {
-            const unsigned jj = chunk_base + lane;
-            const size_t v = r.items.voxel(jj);
-            if (r.items.stage) {
-              // normalised already
-              float cv[K];
-              const float cn = load_staged<N>(r.items.stage, v, cv);
-#pragma unroll
-              for (int k = 0; k < K; ++k) cs[k][lane] = cv[k];
-              cz[lane] = cn;
-            } else {
-              float cv[K];
-              const float cn = load_tensor<N>(a, v, cv);
-#pragma unroll
-              for (int k = 0; k < K; ++k) cs[k][lane] = cv[k];
-              const float inv = cn > 0.0f ? 1.0f / cn : 0.0f;
-#pragma unroll
-              for (int k = 0; k < K; ++k) cs[k][lane] *= inv;
-              cz[lane] = cn;
-            }
-            ca[lane] = w.alpha[jj];
-            if constexpr (CONT) {
-              cu[lane] = w.cont_state[v];
-              ci[lane] = w.cont_it[v] & ((1 << 30) - 1);
-            }
-          }
-          __syncthreads();
-        }
-        const int avail = chunk_runs - next_q;
-        const int take = n_wait < avail ? n_wait : avail;
-        if (!busy) {
-          const int rank = __popcll(waiting & ((1ull << lane) - 1ull));
-          if (rank < take) {
-            const int q = next_q + rank;
-            const int jl = q / R;
-            s = q % R;
-            j = chunk_base + jl;
-            if (cz[jl] > 0.0f) {
-#pragma unroll
-              for (int k = 0; k < K; ++k) c[k] = cs[k][jl];
-              alpha = ca[jl];
-              if constexpr (CONT) {
-                const float4 sv = cu[jl];
-                ux = sv.x; uy = sv.y; uz = sv.z;
-                iters = ci[jl];
-              } else {
-                const float sx = st[3 * (r.s0 + s)], sy_ = st[3 * (r.s0 + s) + 1],
-                            sz = st[3 * (r.s0 + s) + 2];
-                const float rs = 1.0f / sqrtf(sx * sx + sy_ * sy_ + sz * sz);
-                ux = sx * rs; uy = sy_ * rs; uz = sz * rs;
-                iters = 0;
-              }
-              first = true;
-              busy = true;
-              ++n_runs;
-            } else {
-              w.res[(size_t)s * a.plane + j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-              if constexpr (CONT) w.conv[j] = 1;
-            }
-          }
-        }
-        next_q += take;
-        waiting = __ballot(!busy);
-        n_wait = __popcll(waiting);
-      }
+  long long n_steps = 0;
+  unsigned n_runs = 0;
+  auto step = [&] {              // of a run under way
+    float g0, g1, g2;
+    contract<N>(c, ux, uy, uz, g0, g1, g2);
+    const float lam_new = fmaf(g2, uz, fmaf(g0, ux, g1 * uy));
+    dlam = fabsf(lam_new - lam);
+    lam = lam_new;
+    if (!(dlam <= a.tol) && left > 0) {
+      --left;
+      const float wx = fmaf(alpha, ux, g0), wy = fmaf(alpha, uy, g1), wz = fmaf(alpha, uz, g2);
+      const float rn = rsqrt_wave(fmaf(wz, wz, fmaf(wx, wx, wy * wy)));
+      ux = wx * rn; uy = wy * rn; uz = wz * rn;
+    } else {
+      left = ~left;
     }
-    if (busy) {
-      if (!first) {
-        const float wx = fmaf(alpha, ux, g0), wy = fmaf(alpha, uy, g1), wz = fmaf(alpha, uz, g2);
-        const float rn = rsqrtf(wx * wx + wy * wy + wz * wz);
-        ux = wx * rn; uy = wy * rn; uz = wz * rn;
+  };
+  auto put = [&] {               // of an ended run
+    *out = make_float4(ux, uy, uz, lam);
+    if constexpr (CONT) w.conv[j] = dlam <= a.tol ? 1 : 0;
+    out = nullptr;
+    n_steps -= ~left;
+  };
+  while (true) {
+    if (left < 0 && out) put();
+    unsigned long long waiting = __ballot(left < 0);
+    int n_wait = __popcll(waiting);
+    while (n_wait > 0) {
+      if (next_q == chunk_runs) {
+        if (exhausted) break;
+        // next chunk of items
+        unsigned long long base = 0;
+        if (lane == 0) base = atomicAdd(r.ctr, (unsigned long long)chunk);
+        base = (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(base >> 32)) << 32 |
+               (unsigned)__builtin_amdgcn_readfirstlane((int)base);
+        if (base >= n_items) {
+          exhausted = true;
+          break;
+        }
+        const int cnt = (n_items - base) < chunk ? (int)(n_items - base) : (int)chunk;
+        if (base + chunk >= n_items) exhausted = true;
+        chunk_base = (unsigned)base;
+        chunk_runs = cnt * R;
+        next_q = 0;
+        wave_sync();   // earlier LDS reads of the previous chunk are complete
+        if (lane < cnt) {
+          const unsigned jj = chunk_base + lane;
+          const size_t v = r.items.voxel(jj);
+          if (r.items.stage) {
+            // normalised already
+            float cv[K];
+            const float cn = load_staged<N>(r.items.stage, v, cv);
+#pragma unroll
+            for (int k = 0; k < K; ++k) cs[k][lane] = cv[k];
+            cz[lane] = cn;
+          } else {
+            float cv[K];
+            const float cn = load_tensor<N>(a, v, cv);
+            const float inv = cn > 0.0f ? 1.0f / cn : 0.0f;
+#pragma unroll
+            for (int k = 0; k < K; ++k) cs[k][lane] = cv[k] * inv;
+            cz[lane] = cn;
+          }
+          ca[lane] = w.alpha[jj];
+          if constexpr (CONT) {
+            cu[lane] = w.cont_state[v];
+            ci[lane] = w.cont_it[v] & ((1 << 30) - 1);
+          }
+        }
+        wave_sync();
       }
-      contract<N>(c, ux, uy, uz, g0, g1, g2);
-      const float lam_new = g0 * ux + g1 * uy + g2 * uz;
-      bool conv = false, end = false;
-      if (first) {
-        first = false;
-      } else {
-        ++iters;
-        ++n_steps;
-        conv = fabsf(lam_new - lam) <= a.tol;
-        end = conv || iters >= a.max_iter;
+      const int avail = chunk_runs - next_q;
+      const int take = n_wait < avail ? n_wait : avail;
+      const int rank = __popcll(waiting & ((1ull << lane) - 1ull));
+      if (left < 0 && rank < take) {
+        const unsigned q = (unsigned)(next_q + rank);
+        const int jl = CONT ? (int)q : (int)(q * rdiv >> 20);
+        const int s = (int)q - jl * R;
+        j = chunk_base + jl;
+        out = w.res + ((size_t)s * a.plane + j);
+        if (cz[jl] > 0.0f) {
+#pragma unroll
+          for (int k = 0; k < K; ++k) c[k] = cs[k][jl];
+          alpha = ca[jl];
+          left = a.max_iter;
+          if constexpr (CONT) {
+            const float4 sv = cu[jl];
+            ux = sv.x; uy = sv.y; uz = sv.z;
+            left = max(a.max_iter - ci[jl], 1);
+          } else {
+            ux = st[0][s]; uy = st[1][s]; uz = st[2][s];
+          }
+          n_steps += left;
+          lam = __builtin_nanf("");   // the first lambda is no convergence
+          ++n_runs;
+        } else {
+          *out = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+          if constexpr (CONT) w.conv[j] = 1;
+          out = nullptr;
+        }
       }
-      lam = lam_new;
-      if (end) {
-        w.res[(size_t)s * a.plane + j] = make_float4(ux, uy, uz, lam);
-        if constexpr (CONT) w.conv[j] = conv ? 1 : 0;
-        busy = false;
-      }
+      next_q += take;
+      waiting = __ballot(left < 0);
+      n_wait = __popcll(waiting);
+    }
+    const bool drained = exhausted && next_q == chunk_runs;
+    if (drained && n_wait >= 64 - kRest) break;
+    const int limit = drained ? 64 - kRest : kRefill;
+    do {
+      if (left >= 0) step();
+      n_wait = __popcll(__ballot(left < 0));
+    } while (n_wait < limit);
+  }
+  // the workgroup's last runs, gathered in its first wavefront: the longest take
+  // max_iter updates, with a few lanes of every wavefront on the chip otherwise
+  float* rest = &cs[0][0];
+  if (left >= 0) {
+    float* p = rest + __popcll(__ballot(true) & ((1ull << lane) - 1ull));
+#pragma unroll
+    for (int k = 0; k < K; ++k) p[k * kRest] = c[k];
+    p[K * kRest] = alpha;
+    p[(K + 1) * kRest] = ux; p[(K + 2) * kRest] = uy; p[(K + 3) * kRest] = uz;
+    p[(K + 4) * kRest] = lam;
+    p[(K + 5) * kRest] = __int_as_float(left);
+    p[(K + 6) * kRest] = __uint_as_float((unsigned)(size_t)out);
+    p[(K + 7) * kRest] = __uint_as_float((unsigned)((size_t)out >> 32));
+    p[(K + 8) * kRest] = __uint_as_float(j);
+  }
+  const int n_busy = __popcll(__ballot(left >= 0));
+  if (lane == 0) n_rest[wave] = n_busy;
+  __syncthreads();
+  if (wave == 0) {
+    const int from = lane / kRest, at = lane % kRest;
+    if (at < n_rest[from]) {
+      const float* p = &cs_all[from][0][0] + at;
+#pragma unroll
+      for (int k = 0; k < K; ++k) c[k] = p[k * kRest];
+      alpha = p[K * kRest];
+      ux = p[(K + 1) * kRest]; uy = p[(K + 2) * kRest]; uz = p[(K + 3) * kRest];
+      lam = p[(K + 4) * kRest];
+      left = __float_as_int(p[(K + 5) * kRest]);
+      out = reinterpret_cast<float4*>((size_t)__float_as_uint(p[(K + 6) * kRest]) |
+                                      (size_t)__float_as_uint(p[(K + 7) * kRest]) << 32);
+      j = __float_as_uint(p[(K + 8) * kRest]);
+      while (left >= 0) step();
+      put();
     }
   }
   if (a.counters) {
-    count_add(a.counters + 0, n_steps);
+    count_add(a.counters + 0, (unsigned long long)n_steps);
     count_add(a.counters + 4, n_runs);
   }
 }
@@ -1172,7 +1259,7 @@ int launch_multistart(const ExtractArgs& a, Items it, unsigned long long* ctr_ba
     const int nsb = (a.n_starts - b * kStartBlock) < kStartBlock ? (a.n_starts - b * kStartBlock)
                                                                  : kStartBlock;
     RunArgs r{it, nsb, b * kStartBlock, ctr_base + b};
-    hipLaunchKernelGGL((k_runs<N, false>), dim3(kPoolGroups), dim3(64), 0, s, a, r);
+    hipLaunchKernelGGL((k_runs<N, false>), dim3(pool_groups(a.plane * nsb)), dim3(64 * kPoolWaves), 0, s, a, r);
     hipLaunchKernelGGL(k_reduce<N>, dim3(nb), dim3(256), 0, s, a, it, nsb, b == 0 ? 1 : 0,
                        b == n_blocks - 1 ? 1 : 0, merge);
   }
@@ -1203,7 +1290,7 @@ int launch_n(const ExtractArgs& a, hipStream_t s) {
           const unsigned ib = nb < kItemGroups ? nb : kItemGroups;
           hipLaunchKernelGGL((k_prepare<N>), dim3(ib), dim3(256), 0, s, a, cont, 0, 0);
           RunArgs r{cont, 1, 0, ctr + kHdrPoolCont / 2};
-          hipLaunchKernelGGL((k_runs<N, true>), dim3(kPoolGroups), dim3(64), 0, s, a, r);
+          hipLaunchKernelGGL((k_runs<N, true>), dim3(pool_groups(a.plane)), dim3(64 * kPoolWaves), 0, s, a, r);
           hipLaunchKernelGGL(k_learned_post<N>, dim3(ib), dim3(256), 0, s, a);
           compact(w, a.plane, 2, w.fb_list, &w.hdr[kHdrFallbacks], s);
           launch_multistart<N>(a, Items{w.fb_list, &w.hdr[kHdrFallbacks], w.stage}, ctr + kHdrPoolFb / 2,

@@ -251,3 +251,60 @@ def test_find_peaks_candidates(T, ctx, kind, shape, top, dist):
     ref = _greedy(s, lo, hi, top, dist)
     assert peaks.cpu().numpy().tolist() == [list(p) for p in ref]
     assert np.array_equal(vals.cpu().numpy(), np.array([max(s[p], 0.0) if s[p] == s[p] else 0.0 for p in ref], np.float32))
+
+
+@pytest.mark.parametrize("dprime,n,shape,cuts,n_starts,max_iter", [
+    (3, 2, (1, 1, 1), (), 1, 500),                  # one run
+    (3, 4, (1, 1, 65), (), 17, 500),                # a second start block of one start
+    (3, 4, (27, 30, 30), (1, 9), 16, 500),          # 388 800 runs against 14 400 and more
+    (3, 6, (9, 31, 64), (4,), 33, 3),               # runs that end at max_iter, three start blocks
+    (3, 6, (40, 40, 40), (20,), 16, 500),           # 1 024 000 runs against 512 000
+])
+def test_extract_runs_edges(T, ctx, dprime, n, shape, cuts, n_starts, max_iter):
+    """A run's answer depends on its voxel and start alone: the box extracted
+    whole equals the box in slabs, bit for bit, and takes as many updates.
+    Sampled voxels (a planted direction with noise, one zero tensor) against the
+    64-bit iteration from that direction: FP32 sums of at most 28 terms, 1e-5
+    of lambda, and 0.05 degrees."""
+    import torch
+
+    from oracle import sym
+    from oracle import ttm as orc
+    d = T.make_desc(n, 16, 7.0, dprime=dprime)
+    rng = np.random.default_rng(5)
+    V = int(np.prod(shape))
+    vs = rng.standard_normal((V, dprime))
+    vs /= np.linalg.norm(vs, axis=1, keepdims=True)
+    C = rng.uniform(0.5, 2.0, V)[:, None] * (sym.monomials(vs, n) + 0.004 * rng.standard_normal((V, sym.n_components(n, dprime))))
+    if V > 1:
+        C[V // 2] = 0.0
+    Cg = torch.from_numpy(np.ascontiguousarray(C.T).reshape(-1, *shape)).float().cuda()
+    st = rng.standard_normal((n_starts, dprime))
+    st = torch.from_numpy(st / np.linalg.norm(st, axis=1, keepdims=True)).float().cuda()
+
+    def run(Cf):
+        cnt = torch.zeros(5, dtype=torch.int64, device="cuda")
+        out = T.extract(ctx, d, Cf.contiguous(), starts=st, max_iter=max_iter, counters=cnt)
+        return [x.cpu().numpy() for x in out], cnt.cpu().numpy()
+
+    (score, lam, u), cnt = run(Cg)
+    edges = [0, *cuts, shape[0]]
+    parts = [run(Cg[:, a:b]) for a, b in zip(edges, edges[1:])]
+    for i, whole in enumerate((score, lam, u)):
+        assert np.array_equal(whole, np.concatenate([p[0][i] for p in parts]))
+    assert np.array_equal(cnt, sum(p[1] for p in parts))
+    assert cnt[4] == (V - (V > 1)) * n_starts and cnt[0] <= cnt[4] * max_iter
+    if max_iter < 500:
+        return
+    lam, u = lam.ravel(), u.reshape(-1, dprime)
+    if V > 1:
+        assert lam[V // 2] == 0 and not u[V // 2].any()
+    C64 = Cg.cpu().numpy().reshape(len(C[0]), V).T.astype(np.float64)
+    for v in rng.choice(V, min(V, 24), replace=False):
+        if not C64[v].any():
+            continue
+        ref, ur, *_ = orc.sshopm(C64[v], n, vs[v], 0.0, 1e-15, 500)
+        if n_starts > 1:
+            assert lam[v] >= ref * (1 - 1e-5)
+        if lam[v] <= ref * (1 + 1e-5) and n_starts > 1:
+            assert abs(ur @ u[v]) >= np.cos(np.radians(0.05)) * np.linalg.norm(ur)
