@@ -602,30 +602,6 @@ struct RunArgs {
   unsigned long long* ctr;
 };
 
-// 1 / sqrt(n2) as rsqrtf gives it; its steps for subnormal n2 are taken only by
-// a wavefront that holds one.
-__device__ __forceinline__ float rsqrt_wave(float n2) {
-  if (__ballot(n2 < 0x1p-126f) != 0ull) return rsqrtf(n2);
-  return __builtin_amdgcn_rsqf(n2);
-}
-
-// Orders a wavefront's LDS accesses (its own reads and writes reach LDS in order).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
-// Pooled workgroups for so many runs.  A run of max_iter updates is a serial chain,
-// and it advances at its wavefront's share of the SIMD: few runs end soonest with one
-// wavefront per SIMD (a workgroup per CU), many with all that fit.  Score and
-// orientation of e^3 voxels of degree 4 with 256 / 512 / 1024 / 2048 workgroups:
-// e = 24 (220 000 runs) 226 / 270 / 390 / 419 us, e = 32 (520 000) 322 / 291 / 419 /
-// 646, e = 48 (1.8 million) 725 / 475 / 447 / 593, e = 80 (8.2 million) 2625 / 1578 /
-// 1170 / 1110; degree 6 changes at the same counts.
-__host__ __device__ inline unsigned pool_groups(size_t runs) {
-  return runs < 350000 ? 256 : runs < 1000000 ? 512 : runs < 4000000 ? 1024 : 2048;
-}
-
 template <int N, bool CONT>
 __global__ __launch_bounds__(64 * kPoolWaves) void k_runs(ExtractArgs a, RunArgs r) {
   constexpr int K = ncomp3(N);

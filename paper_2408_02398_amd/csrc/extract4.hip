@@ -37,7 +37,6 @@ namespace ttm {
 namespace {
 
 constexpr int kRefill4 = 8;        // a pooled wavefront refills once this many lanes wait
-constexpr int kPoolGroups4 = 4096; // persistent pooled grid (one wavefront per group)
 constexpr int kStartBlock4 = 16;   // starts whose run results are held at once
 constexpr unsigned kItemGroups4 = 1024;
 constexpr float kShiftMargin4 = 1e-5f;
@@ -378,27 +377,54 @@ __global__ __launch_bounds__(256) void k_prepare4(ExtractArgs a, Items4 it) {
   if (a.counters) count_add4(a.counters + 3, n_shift);
 }
 
+// Wavefronts of a pooled workgroup: as many as its staged tensors leave room for.
+__host__ __device__ constexpr int pool_waves4(int N) { return N <= 4 ? 4 : 2; }
+
 // Persistent pooled SS-HOPM runs over (item, start) pairs: run q of a chunk
 // is item chunk_base + q / R with start s0 + q % R.  A wavefront takes up to
 // 64 voxels at a time from a global counter and stages their normalised
 // tensors and shifts in LDS; lanes whose run has ended take the chunk's next
 // runs as soon as kRefill4 of them wait.  A run ends at |delta lambda| <= tol
 // or max_iter updates; its (u, lambda) goes to slot (q % R) * plane + item.
+// Bound by vector issue and, for few runs, by the longest ones, as the axis form's
+// pool: the step's loop holds the step alone, the workgroup's last runs gather in
+// one wavefront, and the run count sets the workgroups.  Localising 125 copies
+// (15 375 voxels, 16 starts at a time, degree 4): 338 -> 140 us a launch.
 template <int N>
-__global__ __launch_bounds__(64) void k_runs4(ExtractArgs a, Items4 it, int R, int s0,
-                                              unsigned long long* ctr) {
+__global__ __launch_bounds__(64 * pool_waves4(N)) void k_runs4(ExtractArgs a, Items4 it, int R, int s0,
+                                                               unsigned long long* ctr) {
   constexpr int K = ncomp4(N);
-  constexpr Sym4<N> sy{};
-  __shared__ float st[64 * 4];
-  __shared__ float cs[K][64];
-  __shared__ float ca[64];
-  __shared__ float cz[64];
-  const int lane = threadIdx.x;
-  for (int i = lane; i < a.n_starts * 4; i += 64) st[i] = a.starts[i];
-  __syncthreads();
+  constexpr int W = pool_waves4(N);
+  constexpr int kRest = 64 / W;     // runs a wavefront may hand over
+  constexpr int kState = K + 9;     // words of a run
+  static_assert(kState * kRest <= K * 64, "a wavefront's runs fit its chunk's place");
+  __shared__ float st[4][kStartBlock4];   // this block's starts, normalised
+  __shared__ float cs_all[W][K][64];
+  __shared__ float ca_all[W][64];
+  __shared__ float cz_all[W][64];
+  __shared__ int n_rest[W];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  float (&cs)[K][64] = cs_all[wave];
+  float (&ca)[64] = ca_all[wave];
+  float (&cz)[64] = cz_all[wave];
   const Ws4 w = ws4_layout(a.ws, a.plane);
   const unsigned n_items = (unsigned)it.n(a);
-  const unsigned per_wave = (n_items + 4 * gridDim.x - 1) / (4 * gridDim.x);
+  const unsigned groups = min(gridDim.x, pool_groups((size_t)n_items * R) * (4 / W));
+  if (blockIdx.x >= groups) return;
+  if ((int)threadIdx.x < R) {
+    const float* sv = a.starts + 4 * (s0 + lane);
+    const float rs = 1.0f / sqrtf(sv[0] * sv[0] + sv[1] * sv[1] + sv[2] * sv[2] + sv[3] * sv[3]);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) st[d][lane] = sv[d] * rs;
+  }
+  __syncthreads();
+  // q / R = q * rdiv >> 20 for q < 64 R: with rdiv R = 2^20 + e, e < R <= 16, the
+  // product is off by q e / R < 2^10 < 2^20 / R
+  const unsigned rdiv = ((1u << 20) + R - 1) / R;
+  static_assert(kStartBlock4 <= 16, "the division above");
+  const unsigned parts = 4 * W * groups;
+  const unsigned per_wave = (n_items + parts - 1) / parts;
   const unsigned chunk = per_wave < 1 ? 1 : (per_wave > 64 ? 64 : per_wave);
   unsigned chunk_base = 0;
   int chunk_runs = 0, next_q = 0;
@@ -406,106 +432,138 @@ __global__ __launch_bounds__(64) void k_runs4(ExtractArgs a, Items4 it, int R, i
   float c[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) c[k] = 0.0f;
-  float alpha = 0.0f, u[4] = {0.0f, 0.0f, 0.0f, 0.0f}, g[4] = {0.0f, 0.0f, 0.0f, 0.0f}, lam = 0.0f;
-  int iters = 0, s = 0;
-  unsigned j = 0;
-  bool first = false, busy = false;
-  unsigned long long n_steps = 0, n_runs = 0;
-  while (true) {
-    unsigned long long waiting = __ballot(!busy);
-    int n_wait = __popcll(waiting);
-    if (n_wait == 64 && exhausted && next_q == chunk_runs) break;
-    if (n_wait >= kRefill4 || n_wait == 64) {
-      while (n_wait > 0) {
-        if (next_q == chunk_runs) {
-          if (exhausted) break;
-          unsigned long long base = 0;
-          if (lane == 0) base = atomicAdd(ctr, (unsigned long long)chunk);
-          base = __shfl(base, 0);
-          if (base >= n_items) {
-            exhausted = true;
-            break;
-          }
-          const int cnt = (n_items - base) < chunk ? (int)(n_items - base) : (int)chunk;
-          if (base + chunk >= n_items) exhausted = true;
-          chunk_base = (unsigned)base;
-          chunk_runs = cnt * R;
-          next_q = 0;
-          __syncthreads();   // the previous chunk's LDS reads are complete
-          if (lane < cnt) {
-            const size_t jj = chunk_base + lane;
-            float cv[K];
-            const float cn = load4<N>(a, it.voxel(jj), cv);
-            const float inv = cn > 0.0f ? 1.0f / cn : 0.0f;
+  float alpha = 0.0f, u[4] = {0.0f, 0.0f, 0.0f, 0.0f}, lam = 0.0f;
+  int left = -1;               // updates left of a run under way, ~left of an ended one
+  size_t out = ~(size_t)0;     // slot of the run's answer
+  long long n_steps = 0;
+  unsigned n_runs = 0;
+  auto step = [&] {            // of a run under way
+    float g[4];
+    contract4<N>(c, u, g);
+    const float lam_new = dot4(g, u);
+    const bool conv = fabsf(lam_new - lam) <= a.tol;
+    lam = lam_new;
+    if (!conv && left > 0) {
+      --left;
+      float v[4];
 #pragma unroll
-            for (int k = 0; k < K; ++k) cs[k][lane] = cv[k] * inv;
-            cz[lane] = cn;
-            ca[lane] = w.alpha[jj];
-          }
-          __syncthreads();
-        }
-        const int avail = chunk_runs - next_q;
-        const int take = n_wait < avail ? n_wait : avail;
-        if (!busy) {
-          const int rank = __popcll(waiting & ((1ull << lane) - 1ull));
-          if (rank < take) {
-            const int q = next_q + rank;
-            const int jl = q / R;
-            s = q % R;
-            j = chunk_base + jl;
-            if (cz[jl] > 0.0f) {
+      for (int d = 0; d < 4; ++d) v[d] = fmaf(alpha, u[d], g[d]);
+      const float rn = rsqrt_wave(dot4(v, v));
 #pragma unroll
-              for (int k = 0; k < K; ++k) c[k] = cs[k][jl];
-              alpha = ca[jl];
-              const float* sv = &st[4 * (s0 + s)];
-              const float rs = 1.0f / sqrtf(sv[0] * sv[0] + sv[1] * sv[1] + sv[2] * sv[2] + sv[3] * sv[3]);
-#pragma unroll
-              for (int d = 0; d < 4; ++d) u[d] = sv[d] * rs;
-              iters = 0;
-              first = true;
-              busy = true;
-              ++n_runs;
-            } else {
-              w.res_u[(size_t)s * a.plane + j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-              w.res_l[(size_t)s * a.plane + j] = 0.0f;
-            }
-          }
-        }
-        next_q += take;
-        waiting = __ballot(!busy);
-        n_wait = __popcll(waiting);
-      }
+      for (int d = 0; d < 4; ++d) u[d] = v[d] * rn;
+    } else {
+      left = ~left;
     }
-    if (busy) {
-      if (!first) {
-        float v[4];
+  };
+  auto put = [&] {             // of an ended run
+    w.res_u[out] = make_float4(u[0], u[1], u[2], u[3]);
+    w.res_l[out] = lam;
+    out = ~(size_t)0;
+    n_steps -= ~left;
+  };
+  while (true) {
+    if (left < 0 && out != ~(size_t)0) put();
+    unsigned long long waiting = __ballot(left < 0);
+    int n_wait = __popcll(waiting);
+    while (n_wait > 0) {
+      if (next_q == chunk_runs) {
+        if (exhausted) break;
+        unsigned long long base = 0;
+        if (lane == 0) base = atomicAdd(ctr, (unsigned long long)chunk);
+        base = (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(base >> 32)) << 32 |
+               (unsigned)__builtin_amdgcn_readfirstlane((int)base);
+        if (base >= n_items) {
+          exhausted = true;
+          break;
+        }
+        const int cnt = (n_items - base) < chunk ? (int)(n_items - base) : (int)chunk;
+        if (base + chunk >= n_items) exhausted = true;
+        chunk_base = (unsigned)base;
+        chunk_runs = cnt * R;
+        next_q = 0;
+        wave_sync();   // the previous chunk's LDS reads are complete
+        if (lane < cnt) {
+          const size_t jj = chunk_base + lane;
+          float cv[K];
+          const float cn = load4<N>(a, it.voxel(jj), cv);
+          const float inv = cn > 0.0f ? 1.0f / cn : 0.0f;
 #pragma unroll
-        for (int d = 0; d < 4; ++d) v[d] = fmaf(alpha, u[d], g[d]);
-        const float rn = rsqrtf(dot4(v, v));
+          for (int k = 0; k < K; ++k) cs[k][lane] = cv[k] * inv;
+          cz[lane] = cn;
+          ca[lane] = w.alpha[jj];
+        }
+        wave_sync();
+      }
+      const int avail = chunk_runs - next_q;
+      const int take = n_wait < avail ? n_wait : avail;
+      const int rank = __popcll(waiting & ((1ull << lane) - 1ull));
+      if (left < 0 && rank < take) {
+        const unsigned q = (unsigned)(next_q + rank);
+        const int jl = (int)(q * rdiv >> 20);
+        const int s = (int)q - jl * R;
+        out = (size_t)s * a.plane + (chunk_base + jl);
+        if (cz[jl] > 0.0f) {
 #pragma unroll
-        for (int d = 0; d < 4; ++d) u[d] = v[d] * rn;
+          for (int k = 0; k < K; ++k) c[k] = cs[k][jl];
+          alpha = ca[jl];
+#pragma unroll
+          for (int d = 0; d < 4; ++d) u[d] = st[d][s];
+          left = a.max_iter;
+          n_steps += left;
+          lam = __builtin_nanf("");   // the first lambda is no convergence
+          ++n_runs;
+        } else {
+          w.res_u[out] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+          w.res_l[out] = 0.0f;
+          out = ~(size_t)0;
+        }
       }
-      contract4<N>(c, u, g);
-      const float lam_new = dot4(g, u);
-      bool end = false;
-      if (first) {
-        first = false;
-      } else {
-        ++iters;
-        ++n_steps;
-        end = fabsf(lam_new - lam) <= a.tol || iters >= a.max_iter;
-      }
-      lam = lam_new;
-      if (end) {
-        w.res_u[(size_t)s * a.plane + j] = make_float4(u[0], u[1], u[2], u[3]);
-        w.res_l[(size_t)s * a.plane + j] = lam;
-        busy = false;
-      }
+      next_q += take;
+      waiting = __ballot(left < 0);
+      n_wait = __popcll(waiting);
+    }
+    const bool drained = exhausted && next_q == chunk_runs;
+    if (drained && n_wait >= 64 - kRest) break;
+    const int limit = drained ? 64 - kRest : kRefill4;
+    do {
+      if (left >= 0) step();
+      n_wait = __popcll(__ballot(left < 0));
+    } while (n_wait < limit);
+  }
+  // the workgroup's last runs, gathered in its first wavefront
+  if (left >= 0) {
+    float* p = &cs[0][0] + __popcll(__ballot(true) & ((1ull << lane) - 1ull));
+#pragma unroll
+    for (int k = 0; k < K; ++k) p[k * kRest] = c[k];
+    p[K * kRest] = alpha;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) p[(K + 1 + d) * kRest] = u[d];
+    p[(K + 5) * kRest] = lam;
+    p[(K + 6) * kRest] = __int_as_float(left);
+    p[(K + 7) * kRest] = __uint_as_float((unsigned)out);
+    p[(K + 8) * kRest] = __uint_as_float((unsigned)(out >> 32));
+  }
+  const int n_busy = __popcll(__ballot(left >= 0));
+  if (lane == 0) n_rest[wave] = n_busy;
+  __syncthreads();
+  if (wave == 0) {
+    const int from = lane / kRest, at = lane % kRest;
+    if (at < n_rest[from]) {
+      const float* p = &cs_all[from][0][0] + at;
+#pragma unroll
+      for (int k = 0; k < K; ++k) c[k] = p[k * kRest];
+      alpha = p[K * kRest];
+#pragma unroll
+      for (int d = 0; d < 4; ++d) u[d] = p[(K + 1 + d) * kRest];
+      lam = p[(K + 5) * kRest];
+      left = __float_as_int(p[(K + 6) * kRest]);
+      out = (size_t)__float_as_uint(p[(K + 7) * kRest]) | (size_t)__float_as_uint(p[(K + 8) * kRest]) << 32;
+      while (left >= 0) step();
+      put();
     }
   }
-  (void)sy;
   if (a.counters) {
-    count_add4(a.counters + 0, n_steps);
+    count_add4(a.counters + 0, (unsigned long long)n_steps);
     count_add4(a.counters + 4, n_runs);
   }
 }
@@ -789,8 +847,8 @@ void launch_multistart4(const ExtractArgs& a, const Items4& it, int merge, hipSt
   for (int b = 0; b < n_blocks; ++b) {
     const int nsb = (a.n_starts - b * kStartBlock4) < kStartBlock4 ? (a.n_starts - b * kStartBlock4)
                                                                    : kStartBlock4;
-    hipLaunchKernelGGL(k_runs4<N>, dim3(kPoolGroups4), dim3(64), 0, s, a, it, nsb, b * kStartBlock4,
-                       w.ctr + b);
+    hipLaunchKernelGGL(k_runs4<N>, dim3(pool_groups(a.plane * nsb) * (4 / pool_waves4(N))),
+                       dim3(64 * pool_waves4(N)), 0, s, a, it, nsb, b * kStartBlock4, w.ctr + b);
     hipLaunchKernelGGL(k_reduce4<N>, dim3(ib), dim3(256), 0, s, a, it, nsb, b == 0 ? 1 : 0,
                        b == n_blocks - 1 ? 1 : 0, merge);
   }

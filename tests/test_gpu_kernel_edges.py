@@ -259,12 +259,15 @@ def test_find_peaks_candidates(T, ctx, kind, shape, top, dist):
     (3, 4, (27, 30, 30), (1, 9), 16, 500),          # 388 800 runs against 14 400 and more
     (3, 6, (9, 31, 64), (4,), 33, 3),               # runs that end at max_iter, three start blocks
     (3, 6, (40, 40, 40), (20,), 16, 500),           # 1 024 000 runs against 512 000
+    (4, 2, (3, 5, 7), (1,), 5, 500),
+    (4, 4, (24, 30, 32), (10,), 16, 500),           # 368 640 runs against 153 600 and 215 040
+    (4, 6, (5, 9, 17), (2, 3), 18, 4),              # pairs of wavefronts, a block of two starts
 ])
 def test_extract_runs_edges(T, ctx, dprime, n, shape, cuts, n_starts, max_iter):
     """A run's answer depends on its voxel and start alone: the box extracted
     whole equals the box in slabs, bit for bit, and takes as many updates.
     Sampled voxels (a planted direction with noise, one zero tensor) against the
-    64-bit iteration from that direction: FP32 sums of at most 28 terms, 1e-5
+    64-bit iteration from that direction: FP32 sums of at most 56 terms, 1e-5
     of lambda, and 0.05 degrees."""
     import torch
 
