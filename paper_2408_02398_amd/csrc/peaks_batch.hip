@@ -17,6 +17,8 @@
 //                 touches are updated: emptied when they lie inside it,
 //                 rescanned without the excluded voxels when their smallest
 //                 key's voxel was excluded, and otherwise left as they are.
+//   k_nms_lds     the same for items of few peaks whose block keys fit LDS, a
+//                 block rescanned only once its key comes up (below).
 // Every item's work is independent, so one launch serves the whole batch.
 #include "../../include/ttm.h"
 #include "internal.hpp"
@@ -72,7 +74,7 @@ __host__ __device__ inline void scratch_layout(void* base, const ItemGeo& g,
 __device__ __forceinline__ unsigned long long voxel_key(const ttm_peak_item& it, const ItemGeo& g,
                                                         const unsigned* bits, int vz, int vy, int vx) {
   const size_t vi = ((size_t)vz * g.vy + vy) * g.vx + vx;
-  if ((bits[vi >> 5] >> (vi & 31)) & 1u) return ~0ull;
+  if (bits && ((bits[vi >> 5] >> (vi & 31)) & 1u)) return ~0ull;
   const int z = it.valid_lo[0] + vz, y = it.valid_lo[1] + vy, x = it.valid_lo[2] + vx;
   const size_t lin = ((size_t)z * it.dims[1] + y) * it.dims[2] + x;
   return ((unsigned long long)(~sbits(it.score[lin])) << 32) | (unsigned long long)lin;
@@ -114,7 +116,7 @@ __global__ __launch_bounds__(512) void k_block_keys(const ttm_peak_item* __restr
   unsigned long long* keys;
   unsigned* bits;
   scratch_layout(it.scratch, g, &keys, &bits);
-  unsigned long long m = block_min(it, g, bits, b, threadIdx.x, 512);
+  unsigned long long m = block_min(it, g, nullptr, b, threadIdx.x, 512);   // nothing excluded yet
   m = wave_min(m);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
   __syncthreads();
@@ -125,10 +127,149 @@ __global__ __launch_bounds__(512) void k_block_keys(const ttm_peak_item* __restr
   }
 }
 
-__global__ __launch_bounds__(256) void k_clear_bits(const ttm_peak_item* __restrict__ items) {
+// Items of k_nms_lds: at most kLdsPeaks peaks (each check of a voxel looks at all
+// kept ones, a lane each) and `cap` blocks, the launch's LDS.
+constexpr int kLdsPeaks = 512;
+constexpr int kLdsBlocks = 18432;       // 144 KB of keys: 211^3 voxels
+__device__ __forceinline__ bool in_lds(const ttm_peak_item& it, const ItemGeo& g, int cap) {
+  return it.top_p <= kLdsPeaks && (long long)g.bz * g.by * g.bx <= cap;
+}
+
+// A workgroup per item, its block keys in LDS.  A key is a lower bound once
+// exclusion has removed its voxel, and a block whose key never comes up is never
+// rescanned.  In each step every wavefront takes the smallest key of its own
+// blocks and tests that voxel against the kept peaks (no bitmask); when it is
+// excluded the wavefront rescans the block.  The smallest of the wavefronts' keys
+// is the next peak when its voxel was not excluded.  Then blocks inside the
+// peak's ball are emptied.  Each step keeps a peak or raises a key, so it ends.
+// One workgroup per item, so a chain of latencies: rescanning every touched block
+// at once (some 300 of a ball of radius 28, by 16 wavefronts) and the bitmask's
+// atomics took 33 us a peak on 160^3 voxels, this 4.5 us.
+__global__ __launch_bounds__(kNmsThreads) void k_nms_lds(const ttm_peak_item* __restrict__ items, int cap) {
+  constexpr int W = kNmsThreads / 64;
+  extern __shared__ unsigned long long keys[];
+  __shared__ ushort4 kept[kLdsPeaks];             // z, y, x in the valid box
+  __shared__ unsigned long long red_k[2][W];
+  __shared__ int red_out[2][W];
+  const ttm_peak_item it = items[blockIdx.x];
+  if (!item_ok(it)) return;
+  const ItemGeo g = geo(it.valid_lo, it.valid_hi);
+  if (!in_lds(it, g, cap)) return;
+  unsigned long long* gkeys;
+  unsigned* bits;
+  scratch_layout(it.scratch, g, &gkeys, &bits);
+  const int nb = g.bz * g.by * g.bx;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const unsigned ny = (unsigned)it.dims[1], nx = (unsigned)it.dims[2];
+  const float D2 = it.min_dist * it.min_dist;
+  const int R = (int)ceilf(it.min_dist);
+  for (int b = threadIdx.x; b < nb; b += kNmsThreads) keys[b] = gkeys[b];
+  __syncthreads();
+  int found = 0, par = 0;
+  while (found < it.top_p) {
+    unsigned long long m = ~0ull;
+    for (int b = wave * 64 + lane; b < nb; b += kNmsThreads) m = keys[b] < m ? keys[b] : m;
+    m = wave_min(m);
+    bool out = false;
+    if (m != ~0ull) {                             // uniform in the wavefront
+      const unsigned lin = (unsigned)m, r = lin / nx, z = r / ny;
+      const int vz = (int)z - it.valid_lo[0], vy = (int)(r - z * ny) - it.valid_lo[1],
+                vx = (int)(lin - r * nx) - it.valid_lo[2];
+      for (int k = lane; k - lane < found && !out; k += 64) {
+        bool hit = false;
+        if (k < found) {
+          const int dz = vz - kept[k].x, dy = vy - kept[k].y, dx = vx - kept[k].z;
+          const int d = dz * dz + dy * dy + dx * dx;
+          hit = d == 0 || (float)d < D2;
+        }
+        out = __ballot(hit) != 0ull;
+      }
+      if (out) {
+        // the block's smallest key among the voxels left: lane = (y, x), 8 z each
+        const int qz = vz / kBlk * kBlk, qy = vy / kBlk * kBlk, qx = vx / kBlk * kBlk;
+        const int y = qy + (lane >> 3), x = qx + (lane & 7);
+        const size_t row = ((size_t)it.valid_lo[0] * ny + it.valid_lo[1] + min(y, g.vy - 1)) * nx +
+                           it.valid_lo[2] + min(x, g.vx - 1);
+        float sc[kBlk];
+#pragma unroll
+        for (int t = 0; t < kBlk; ++t) sc[t] = it.score[row + (size_t)min(qz + t, g.vz - 1) * ny * nx];
+        unsigned gone = 0;
+        for (int k0 = 0; k0 < found; k0 += 64) {
+          bool near = false;
+          if (k0 + lane < found) {
+            const ushort4 q = kept[k0 + lane];
+            const int dz = max(max(qz - q.x, q.x - (qz + kBlk - 1)), 0), dy = max(max(qy - q.y, q.y - (qy + kBlk - 1)), 0),
+                      dx = max(max(qx - q.z, q.z - (qx + kBlk - 1)), 0);
+            const int d = dz * dz + dy * dy + dx * dx;
+            near = d == 0 || (float)d < D2;
+          }
+          for (unsigned long long bal = __ballot(near); bal; bal &= bal - 1) {
+            const ushort4 q = kept[k0 + __ffsll((long long)bal) - 1];
+            const int dy = y - q.y, dx = x - q.z, dyx = dy * dy + dx * dx;
+#pragma unroll
+            for (int t = 0; t < kBlk; ++t) {
+              const int dz = qz + t - q.x, d = dz * dz + dyx;
+              gone |= (d == 0 || (float)d < D2 ? 1u : 0u) << t;
+            }
+          }
+        }
+        unsigned long long mm = ~0ull;
+#pragma unroll
+        for (int t = 0; t < kBlk; ++t) {
+          const unsigned long long k = ((unsigned long long)(~sbits(sc[t])) << 32) |
+                                       (unsigned long long)(row + (size_t)(qz + t) * ny * nx);
+          if (y < g.vy && x < g.vx && qz + t < g.vz && !(gone >> t & 1u) && k < mm) mm = k;
+        }
+        mm = wave_min(mm);
+        if (lane == 0) keys[(qz / kBlk * g.by + qy / kBlk) * g.bx + qx / kBlk] = mm;
+      }
+    }
+    if (lane == 0) {
+      red_k[par][wave] = m;
+      red_out[par][wave] = out ? 1 : 0;
+    }
+    __syncthreads();
+    unsigned long long best = red_k[par][0];
+    int best_out = red_out[par][0];
+    for (int i = 1; i < W; ++i)
+      if (red_k[par][i] < best) {
+        best = red_k[par][i];
+        best_out = red_out[par][i];
+      }
+    par ^= 1;
+    if (best == ~0ull) break;                     // nothing left
+    if (best_out) continue;                       // a lower bound only: its block has been rescanned
+    const unsigned lin = (unsigned)best, r = lin / nx, z = r / ny, y = r - z * ny, x = lin - r * nx;
+    const int vz = (int)z - it.valid_lo[0], vy = (int)y - it.valid_lo[1], vx = (int)x - it.valid_lo[2];
+    if (threadIdx.x == 0) {
+      it.peaks[3 * found] = (int)z;
+      it.peaks[3 * found + 1] = (int)y;
+      it.peaks[3 * found + 2] = (int)x;
+      it.vals[found] = it.score[lin];
+      kept[found] = make_ushort4((unsigned short)vz, (unsigned short)vy, (unsigned short)vx, 0);
+    }
+    ++found;
+    // blocks whose farthest voxel lies in the ball
+    const int bz0 = max(vz - R, 0) / kBlk, nbz = min(vz + R, g.vz - 1) / kBlk - bz0 + 1;
+    const int by0 = max(vy - R, 0) / kBlk, nby = min(vy + R, g.vy - 1) / kBlk - by0 + 1;
+    const int bx0 = max(vx - R, 0) / kBlk, nbx = min(vx + R, g.vx - 1) / kBlk - bx0 + 1;
+    for (int q = threadIdx.x; q < nbz * nby * nbx; q += kNmsThreads) {
+      const int qz = bz0 + q / (nby * nbx), qy = by0 + (q / nbx) % nby, qx = bx0 + q % nbx;
+      const int fz = max(vz - qz * kBlk, min(qz * kBlk + kBlk, g.vz) - 1 - vz),
+                fy = max(vy - qy * kBlk, min(qy * kBlk + kBlk, g.vy) - 1 - vy),
+                fx = max(vx - qx * kBlk, min(qx * kBlk + kBlk, g.vx) - 1 - vx);
+      if ((float)(fz * fz + fy * fy + fx * fx) < D2) keys[(qz * g.by + qy) * g.bx + qx] = ~0ull;
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) *it.n_found = found;
+}
+
+__global__ __launch_bounds__(256) void k_clear_bits(const ttm_peak_item* __restrict__ items, int cap) {
   const ttm_peak_item it = items[blockIdx.y];
   if (!item_ok(it)) return;
   const ItemGeo g = geo(it.valid_lo, it.valid_hi);
+  if (in_lds(it, g, cap)) return;
   unsigned long long* keys;
   unsigned* bits;
   scratch_layout(it.scratch, g, &keys, &bits);
@@ -136,7 +277,7 @@ __global__ __launch_bounds__(256) void k_clear_bits(const ttm_peak_item* __restr
     bits[w] = 0u;
 }
 
-__global__ __launch_bounds__(kNmsThreads) void k_nms(const ttm_peak_item* __restrict__ items) {
+__global__ __launch_bounds__(kNmsThreads) void k_nms(const ttm_peak_item* __restrict__ items, int cap) {
   __shared__ unsigned long long red_k[kNmsThreads / 64];
   __shared__ unsigned long long s_best;
   const ttm_peak_item it = items[blockIdx.x];
@@ -145,6 +286,7 @@ __global__ __launch_bounds__(kNmsThreads) void k_nms(const ttm_peak_item* __rest
     return;
   }
   const ItemGeo g = geo(it.valid_lo, it.valid_hi);
+  if (in_lds(it, g, cap)) return;
   unsigned long long* keys;
   unsigned* bits;
   scratch_layout(it.scratch, g, &keys, &bits);
@@ -271,10 +413,12 @@ int find_peaks_batch(const ttm_peak_item* items, int n_items, const int32_t max_
   const ItemGeo g = geo(zero, hi);
   const int max_blocks = g.bz * g.by * g.bx;
   const size_t max_words = g.words;
+  const int cap = max_blocks < kLdsBlocks ? max_blocks : kLdsBlocks;
   const unsigned cw = (unsigned)((max_words + 255) / 256);
-  hipLaunchKernelGGL(k_clear_bits, dim3(cw < 4096 ? cw : 4096, n_items), dim3(256), 0, s, items);
+  hipLaunchKernelGGL(k_clear_bits, dim3(cw < 256 ? cw : 256, n_items), dim3(256), 0, s, items, cap);
   hipLaunchKernelGGL(k_block_keys, dim3(max_blocks, n_items), dim3(512), 0, s, items);
-  hipLaunchKernelGGL(k_nms, dim3(n_items), dim3(kNmsThreads), 0, s, items);
+  hipLaunchKernelGGL(k_nms_lds, dim3(n_items), dim3(kNmsThreads), (size_t)cap * 8, s, items, cap);
+  hipLaunchKernelGGL(k_nms, dim3(n_items), dim3(kNmsThreads), 0, s, items, cap);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? 0 : hip_status(e, "find peaks batch launch");
 }

@@ -311,3 +311,49 @@ def test_extract_runs_edges(T, ctx, dprime, n, shape, cuts, n_starts, max_iter):
             assert lam[v] >= ref * (1 - 1e-5)
         if lam[v] <= ref * (1 + 1e-5) and n_starts > 1:
             assert abs(ur @ u[v]) >= np.cos(np.radians(0.05)) * np.linalg.norm(ur)
+
+
+@pytest.mark.parametrize("kind,shape,lo,hi,top,dist", [
+    ("ties", (17, 25, 9), (0, 0, 0), (16, 24, 8), 512, 0.0),          # the most peaks of the keys in LDS
+    ("ties", (17, 25, 9), (0, 0, 0), (16, 24, 8), 513, 0.0),          # one more
+    ("ties", (40, 33, 70), (3, 0, 5), (39, 31, 60), 90, 7.3),         # many equal scores, ragged blocks
+    ("flat", (24, 24, 24), (0, 0, 0), (23, 23, 23), 40, 9.0),         # one score: linear order, blocks emptied
+    ("negative", (9, 10, 11), (1, 1, 1), (8, 8, 8), 30, 2.5),         # scores of 0 and less rank alike
+    ("ties", (1, 1, 40), (0, 0, 0), (0, 0, 39), 9, 1.5),
+    ("blobs", (208, 216, 216), (0, 0, 0), (207, 215, 215), 25, 28.0),  # 18 954 blocks: keys in global memory
+    ("blobs", (200, 208, 208), (1, 1, 1), (199, 206, 207), 25, 28.0),  # 16 900: in LDS
+])
+def test_find_peaks_batch_edges(T, ctx, kind, shape, lo, hi, top, dist):
+    """Find Peaks of a batch (the map, and a second of one voxel) is the greedy
+    rule's result exactly."""
+    import torch
+    rng = np.random.default_rng(3)
+    s = rng.uniform(0, 1, shape).astype(np.float32)
+    if kind == "ties":
+        s = np.round(s, 2)
+    elif kind == "flat":
+        s[:] = 0.5
+    elif kind == "negative":
+        s = np.round(s - 0.6, 1)
+    elif kind == "blobs":
+        from scipy.ndimage import gaussian_filter
+        s = gaussian_filter(s, 3.0).astype(np.float32)
+    one = np.full((1, 1, 1), 2.0, np.float32)
+
+    def entry(a, lo, hi, top, dist):
+        return dict(score=torch.from_numpy(a).cuda(), lo=lo, hi=hi, top_p=top, min_dist=dist,
+                    peaks=torch.zeros((top, 3), dtype=torch.int32, device="cuda"),
+                    vals=torch.zeros(top, dtype=torch.float32, device="cuda"),
+                    n_found=torch.zeros(1, dtype=torch.int32, device="cuda"))
+    es = [entry(s, lo, hi, top, dist), entry(one, (0, 0, 0), (0, 0, 0), 3, 1.0)]
+    pb = T.PeakBatch(ctx, es)
+    for _ in range(2):
+        pb.run()
+        torch.cuda.synchronize()
+        for e, a in zip(es, (s, one)):
+            ref = _greedy(np.maximum(a, 0.0), e["lo"], e["hi"], e["top_p"], e["min_dist"])
+            n = int(e["n_found"].item())
+            assert n == len(ref)
+            got = e["peaks"][:n].cpu().numpy()
+            assert np.array_equal(got, np.asarray(ref).reshape(-1, 3))
+            assert np.array_equal(e["vals"][:n].cpu().numpy(), a[tuple(got.T)])
