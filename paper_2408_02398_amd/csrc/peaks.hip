@@ -352,8 +352,11 @@ struct Settle {
   int* state;                     // 0 undecided, 1 kept, 2 dropped
   unsigned* start;                // first candidate of each cell, ncell + 1
   unsigned* fill;                 // candidates placed per cell
+  unsigned long long* best;       // smallest key of each cell
+  ushort4* lead;                  // its place and w = 1 where it is kept at once
   unsigned m;
   int flat;
+  unsigned per;                   // candidates of a wavefront in a round
   int ny, nx;
   float d2, cell;
   int gz, gy, gx;
@@ -385,6 +388,7 @@ __global__ __launch_bounds__(256) void k_cells(Settle s) {
     if (!s.flat) {
       const int c = cell_of(s, p);
       at = s.start[c] + atomicAdd(&s.fill[c], 1u);
+      atomicMin(&s.best[c], key);
     }
     s.key[at] = key;
     s.pos[at] = p;
@@ -405,20 +409,71 @@ __global__ __launch_bounds__(256) void k_pairs(Settle s) {
       v += s.start[row + min(x + 1, s.gx - 1) + 1] - s.start[row + max(x - 1, 0)];
     }
     v *= s.start[c + 1] - s.start[c];
+    s.best[c] = ~0ull;
   }
   for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off);
   if ((threadIdx.x & 63) == 0 && v) atomicAdd(&s.pick->pairs, v);
 }
 
-// One round, a wavefront per undecided candidate: among the higher-ranked
+// The cells' best candidates with nothing ranked higher within D: they are kept.
+// A wavefront per cell.
+__global__ __launch_bounds__(256) void k_lead(Settle s) {
+  const int c = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const unsigned lane = threadIdx.x & 63;
+  if (c >= s.gz * s.gy * s.gx || s.pick->pairs > kSettlePairs) return;   // uniform per wavefront
+  const int x = c % s.gx, y = (c / s.gx) % s.gy, z = c / (s.gx * s.gy);
+  const unsigned long long own = s.best[c];
+  ushort4 p = key_pos(own, s.ny, s.nx);
+  bool lead = own != ~0ull;
+  for (int o = 0; o < 9 && lead; ++o) {
+    const int z2 = z + o / 3 - 1, y2 = y + o % 3 - 1;
+    if (z2 < 0 || z2 >= s.gz || y2 < 0 || y2 >= s.gy) continue;
+    const int row = (z2 * s.gy + y2) * s.gx;
+    const unsigned e = s.start[row + min(x + 1, s.gx - 1) + 1];
+    for (unsigned j = s.start[row + max(x - 1, 0)] + lane; __ballot(j < e) && lead; j += 64) {
+      bool above = false;
+      if (j < e && s.key[j] < own) {
+        const ushort4 q = s.pos[j];
+        const float ddz = (float)((int)p.x - (int)q.x), ddy = (float)((int)p.y - (int)q.y),
+                    ddx = (float)((int)p.z - (int)q.z);
+        above = ddz * ddz + ddy * ddy + ddx * ddx < s.d2;
+      }
+      lead = __ballot(above) == 0ull;
+    }
+  }
+  p.w = lead ? 1 : 0;
+  if (lane == 0) s.lead[c] = p;
+}
+
+// A thread per candidate: kept when it leads its cell, dropped within D of a leader.
+// Most candidates of a map of peaks are on the slopes of a leader, and this spares
+// them the rounds below.
+__global__ __launch_bounds__(256) void k_drop(Settle s) {
+  const unsigned i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= s.m || s.pick->pairs > kSettlePairs) return;
+  const ushort4 p = s.pos[i];
+  const int hz = (int)(p.x / s.cell), hy = (int)(p.y / s.cell), hx = (int)(p.z / s.cell);
+  int state = 0;
+#pragma unroll
+  for (int o = 0; o < 27; ++o) {
+    const int z2 = min(max(hz + o / 9 - 1, 0), s.gz - 1), y2 = min(max(hy + o / 3 % 3 - 1, 0), s.gy - 1),
+              x2 = min(max(hx + o % 3 - 1, 0), s.gx - 1);
+    const ushort4 q = s.lead[(z2 * s.gy + y2) * s.gx + x2];
+    const float ddz = (float)((int)p.x - (int)q.x), ddy = (float)((int)p.y - (int)q.y),
+                ddx = (float)((int)p.z - (int)q.z);
+    const float d2 = ddz * ddz + ddy * ddy + ddx * ddx;
+    if (q.w) state = d2 == 0.0f ? 1 : (d2 < s.d2 ? 2 : state);
+  }
+  s.state[i] = state;
+}
+
+// One round, a wavefront for `per` candidates (16 where k_drop has left few): among the higher-ranked
 // candidates within D, a kept one drops it, else an undecided one makes it wait
 // for a later round, else it is kept.  States only ever leave 0, so one read too
 // early costs a round and nothing else.  A walk in rank order by one workgroup
-// spent 2.4 ms on 131 000 candidates of 2000 peaks; all rounds of this take 0.34 ms.
-__global__ __launch_bounds__(256) void k_settle(Settle s) {
-  const unsigned i = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const unsigned lane = threadIdx.x & 63;
-  if (i >= s.m || s.pick->pairs > kSettlePairs || s.state[i] != 0) return;   // uniform per wavefront
+// spent 2.4 ms on 131 000 candidates of 2000 peaks, these rounds alone 0.34 ms,
+// and after k_drop they take 16 us (all of Find Peaks on 512 x 512 x 928: 3.76 -> 0.60 ms).
+__device__ __forceinline__ void settle_one(const Settle& s, unsigned i, unsigned lane) {
   const unsigned long long key = s.key[i];
   const ushort4 p = s.pos[i];
   const int hz = (int)(p.x / s.cell), hy = (int)(p.y / s.cell), hx = (int)(p.z / s.cell);
@@ -432,24 +487,44 @@ __global__ __launch_bounds__(256) void k_settle(Settle s) {
       b = s.start[row + max(hx - 1, 0)];
       e = s.start[row + min(hx + 1, s.gx - 1) + 1];
     }
-    for (unsigned j0 = b; j0 < e; j0 += 64) {
-      const unsigned j = j0 + lane;
-      int st = 2;
-      if (j < e && s.key[j] < key) {
-        const ushort4 q = s.pos[j];
-        const float ddz = (float)((int)p.x - (int)q.x), ddy = (float)((int)p.y - (int)q.y),
-                    ddx = (float)((int)p.z - (int)q.z);
-        if (ddz * ddz + ddy * ddy + ddx * ddx < s.d2)
-          st = __hip_atomic_load(&s.state[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (unsigned j0 = b; j0 < e; j0 += 64 * 4) {   // four loads of a lane in flight
+      unsigned long long kj[4];
+      ushort4 q[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const unsigned j = min(j0 + 64 * k + lane, e - 1);
+        kj[k] = s.key[j];
+        q[k] = s.pos[j];
       }
-      if (__ballot(st == 1)) {
+      bool kept = false, undecided = false;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const unsigned j = j0 + 64 * k + lane;
+        const float ddz = (float)((int)p.x - (int)q[k].x), ddy = (float)((int)p.y - (int)q[k].y),
+                    ddx = (float)((int)p.z - (int)q[k].z);
+        if (j < e && kj[k] < key && ddz * ddz + ddy * ddy + ddx * ddx < s.d2) {
+          const int st = __hip_atomic_load(&s.state[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          kept = kept || st == 1;
+          undecided = undecided || st == 0;
+        }
+      }
+      if (__ballot(kept)) {
         if (lane == 0) __hip_atomic_store(&s.state[i], 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
       }
-      wait = wait || __ballot(st == 0) != 0ull;
+      wait = wait || __ballot(undecided) != 0ull;
     }
   }
   if (!wait && lane == 0) __hip_atomic_store(&s.state[i], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__global__ __launch_bounds__(256) void k_settle(Settle s) {
+  const unsigned i0 = (blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6)) * s.per;
+  const unsigned lane = threadIdx.x & 63;
+  if (i0 >= s.m || s.pick->pairs > kSettlePairs) return;   // uniform per wavefront
+  const bool open = lane < s.per && i0 + lane < s.m && s.state[i0 + lane] == 0;
+  for (unsigned long long todo = __ballot(open); todo; todo &= todo - 1)
+    settle_one(s, i0 + (unsigned)__ffsll((long long)todo) - 1, lane);
 }
 
 // Undecided candidates counted, kept ones gathered (the counters cleared before);
@@ -475,9 +550,11 @@ __global__ __launch_bounds__(256) void k_gather(Settle s) {
 __global__ __launch_bounds__(256) void k_rank(const unsigned long long* __restrict__ kept, Pick* pick, int ny, int nx,
                                               int top_p, int* __restrict__ peaks, float* __restrict__ vals) {
   __shared__ unsigned long long tile[1024];
-  const unsigned n = pick->kept, i = blockIdx.x * 256 + threadIdx.x;
-  if (n > kKeptMax || blockIdx.x * 256 >= n) return;   // uniform
-  if (i == 0) pick->n_found = (int)min(n, (unsigned)top_p);
+  __shared__ int part[4][64];
+  const unsigned n = pick->kept;
+  if (n > kKeptMax || blockIdx.x * 64 >= n) return;   // uniform
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const unsigned i = blockIdx.x * 64 + lane;
   const unsigned long long key = i < n ? kept[i] : ~0ull;
   int rank = 0;
   for (unsigned t0 = 0; t0 < n; t0 += 1024) {
@@ -485,8 +562,13 @@ __global__ __launch_bounds__(256) void k_rank(const unsigned long long* __restri
     for (unsigned k = threadIdx.x; k < 1024; k += 256) tile[k] = t0 + k < n ? kept[t0 + k] : ~0ull;
     __syncthreads();
 #pragma unroll 8
-    for (int k = 0; k < 1024; ++k) rank += tile[k] < key ? 1 : 0;
+    for (int k = 0; k < 256; ++k) rank += tile[wave * 256 + k] < key ? 1 : 0;
   }
+  part[wave][lane] = rank;
+  __syncthreads();
+  if (wave) return;
+  rank += part[1][lane] + part[2][lane] + part[3][lane];
+  if (i == 0) pick->n_found = (int)min(n, (unsigned)top_p);
   if (i < n && rank < top_p) {
     const ushort4 p = key_pos(key, ny, nx);
     peaks[3 * rank + 0] = p.x;
@@ -879,10 +961,10 @@ size_t peaks_head_bytes(int64_t n_voxels) {
 constexpr size_t kPeaksTailBytes = (kHashShorts * 2 + 256 + 255) / 256 * 256;
 
 // The settling's arrays behind the tail: positions and states of at most
-// kSettleMax candidates, the cells' starts and fills, the kept keys.
+// kSettleMax candidates, the kept keys, the cells' best keys, leaders, starts and fills.
 size_t settle_bytes(int64_t n_voxels) {
   const size_t m = ((size_t)std::min<int64_t>(n_voxels, kSettleMax) + 1) / 2 * 2;
-  return m * 12 + (2 * kMaxCells + 64) * 4 + (size_t)kKeptMax * 8 + 1024;
+  return m * 12 + (size_t)kMaxCells * 16 + (2 * kMaxCells + 64) * 4 + (size_t)kKeptMax * 8 + 1024;
 }
 
 // The greedy walk over m sorted keys in `srt` (`spare` holds as many):
@@ -1018,7 +1100,9 @@ int find_peaks(const float* score, int nz, int ny, int nx, const int32_t lo[3],
   st.pos = reinterpret_cast<ushort4*>(tail);
   st.state = reinterpret_cast<int*>(tail + sm * 8);
   st.kept = reinterpret_cast<unsigned long long*>(tail + sm * 12);
-  st.start = reinterpret_cast<unsigned*>(st.kept + kKeptMax);
+  st.best = st.kept + kKeptMax;
+  st.lead = reinterpret_cast<ushort4*>(st.best + kMaxCells);
+  st.start = reinterpret_cast<unsigned*>(st.lead + kMaxCells);
   const int ncell = gz * gy * gx;
   st.fill = st.start + ncell + 1;
   Pick* pick = reinterpret_cast<Pick*>(st.start + 2 * kMaxCells + 64);
@@ -1033,13 +1117,14 @@ int find_peaks(const float* score, int nz, int ny, int nx, const int32_t lo[3],
 
   // The threshold comes from a sample of at least 4 million voxels (every 16th
   // (slice, row block) pair of a large map): it only sets how many candidates
-  // there are, not the answer.
+  // there are, not the answer.  A quarter more are asked of a sample, whose count
+  // is off by a few percent: too few candidates cost the whole search once more.
   const int sample = (int)std::min<int64_t>(16, std::max<int64_t>(1, nvalid >> 22));
   Pick got;
   for (int64_t want = std::max<int64_t>(64 * (int64_t)top_p, kFlatMax);; want *= 4) {
     fill_zero(pick, sizeof(Pick), s);
     if (want < nvalid) {
-      const unsigned want_s = (unsigned)std::max<int64_t>(1, want / sample);
+      const unsigned want_s = (unsigned)std::max<int64_t>(1, sample > 1 ? want * 5 / 4 / sample : want);
       for (int level = 0; level < 2; ++level) {
         fill_zero(hist, kHistBins * 4, s);
         hipLaunchKernelGGL(k_hist, hgrid, dim3(256), 0, s, score, r, level, pick, sample, hist);
@@ -1055,6 +1140,7 @@ int find_peaks(const float* score, int nz, int ny, int nx, const int32_t lo[3],
       st.m = (unsigned)m;
       const dim3 mg((unsigned)((m + 255) / 256));
       st.flat = m <= (int64_t)kFlatMax;
+      st.per = st.flat ? 1 : 16;
       if (!st.flat) {
         fill_zero(st.start, (2 * (size_t)ncell + 1) * 4, s);
         hipLaunchKernelGGL(k_cells<false>, mg, dim3(256), 0, s, st);
@@ -1062,13 +1148,17 @@ int find_peaks(const float* score, int nz, int ny, int nx, const int32_t lo[3],
         hipLaunchKernelGGL(k_pairs, dim3((ncell + 255) / 256), dim3(256), 0, s, st);
       }
       if (m > 0) hipLaunchKernelGGL(k_cells<true>, mg, dim3(256), 0, s, st);
+      if (!st.flat) {
+        hipLaunchKernelGGL(k_lead, dim3((ncell + 3) / 4), dim3(256), 0, s, st);
+        hipLaunchKernelGGL(k_drop, mg, dim3(256), 0, s, st);
+      }
       for (int look = 0; look == 0 || (got.undecided && got.pairs <= kSettlePairs && look < kSettleLooks); ++look) {
         fill_zero(&pick->undecided, 8, s);
         if (m > 0) {
           for (int k = 0; k < kSettleRounds; ++k)
-            hipLaunchKernelGGL(k_settle, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, s, st);
+            hipLaunchKernelGGL(k_settle, dim3((unsigned)((m + 4 * st.per - 1) / (4 * st.per))), dim3(256), 0, s, st);
           hipLaunchKernelGGL(k_gather, mg, dim3(256), 0, s, st);
-          hipLaunchKernelGGL(k_rank, dim3(kKeptMax / 256), dim3(256), 0, s, st.kept, pick, ny, nx, top_p,
+          hipLaunchKernelGGL(k_rank, dim3(kKeptMax / 64), dim3(256), 0, s, st.kept, pick, ny, nx, top_p,
                              peaks_out, vals_out);
         }
         TTM_HIP(hipMemcpyAsync(&got, pick, sizeof(Pick), hipMemcpyDeviceToHost, s));
