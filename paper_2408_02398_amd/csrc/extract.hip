@@ -945,7 +945,8 @@ template <int N>
 __global__ __launch_bounds__(64) void k_mlp_start(ExtractArgs a) {
   constexpr int K = ncomp3(N);
   constexpr Sym3<N> sy{};
-  __shared__ unsigned short xs[64 * kMlpIn];
+  __shared__ __align__(8) unsigned short xs[64 * kMlpIn];
+  static_assert(kMlpIn == 32, "two input tiles");
   const int lane = threadIdx.x;
   MlpRegs net;
   load_mlp_regs(a.mlp, lane, net);
@@ -971,9 +972,7 @@ __global__ __launch_bounds__(64) void k_mlp_start(ExtractArgs a) {
     const Vox vr = vox(a, v);
     if ((a.mode & 1) && active && vr.score) vr.score[vr.o] = cn;
     const float inv = cn > 0.0f ? 1.0f / cn : 0.0f;
-#pragma unroll
-    for (int k = 0; k < kMlpIn; ++k)
-      xs[lane * kMlpIn + k] = k < K ? bf16_bits(sqrtf(sy.mu[k]) * c[k] * inv) : (unsigned short)0;
+    put_features<2>(xs, lane, [&](int k) { return k < K ? bf16_bits(sqrtf(sy.mu[k]) * c[k] * inv) : (unsigned short)0; });
     float y0, y1, y2;
     mlp_forward(xs, net, lane, y0, y1, y2);
     const float ny = sqrtf(y0 * y0 + y1 * y1 + y2 * y2);
@@ -995,20 +994,22 @@ __global__ __launch_bounds__(64) void k_mlp_start(ExtractArgs a) {
 // also forces the fallback); each lane then takes up to kNewtonFirst Newton
 // steps from u0.  Converged voxels are screened and written (status 0 or 2),
 // the others marked for SS-HOPM from u0 (status 1, with u0 and its lambda
-// kept per voxel).  Each lane loads its next voxel's tensor before working on
-// the current one, and nothing in the loop waits on a memory result, so the
-// loads' latency hides behind the network and the Newton steps.
+// kept per voxel).
+// Bound by vector issue and, with few wavefronts, by its latency: four wavefronts
+// on a SIMD (128 registers, a few spilled) hide more than the next voxel's tensor
+// loaded ahead did with two, whose network held all 64 voxels' fragments at once
+// (217^3 voxels of degree 6: 1294 -> 1098 us).
 constexpr int kLearnedGroups = 1024;
 constexpr int kLearnedWaves = 4;
 
 template <int N>
-__global__ __launch_bounds__(64 * kLearnedWaves) void k_learned(ExtractArgs a) {
+__global__ __launch_bounds__(64 * kLearnedWaves) __attribute__((amdgpu_waves_per_eu(4))) void k_learned(ExtractArgs a) {
   constexpr int K = ncomp3(N);
   constexpr Sym3<N> sy{};
   __shared__ float st[64 * 3];
   __shared__ float mono[64 * K];
   __shared__ __align__(16) unsigned char pk[kMlpPackedBytes];
-  __shared__ unsigned short xs_all[kLearnedWaves][64 * kMlpIn];
+  __shared__ __align__(8) unsigned short xs_all[kLearnedWaves][64 * kMlpIn];
   static_assert(kMlpPackedBytes % 16 == 0, "packed network copied in 16-byte pieces");
   for (int i = threadIdx.x; i < a.n_starts * 3; i += blockDim.x) st[i] = a.starts[i];
   for (int i = threadIdx.x; i < kMlpPackedBytes / 16; i += blockDim.x)
@@ -1034,19 +1035,11 @@ __global__ __launch_bounds__(64 * kLearnedWaves) void k_learned(ExtractArgs a) {
     const size_t v0 = gi * 64 + lane;
     const bool active = v0 < a.plane;
     const size_t v = active ? v0 : a.plane - 1;
-    float cx[K];
-    const size_t gn = gi + gstride;
-    if (gn < n_groups) {
-      const size_t vn = gn * 64 + lane;
-      load_raw<N>(a, vn < a.plane ? vn : a.plane - 1, cx);
-    }
     const float cn = frob<N>(c);
     const Vox vr = vox(a, v);
     if ((a.mode & 1) && active && vr.score) vr.score[vr.o] = cn;
     const float inv = cn > 0.0f ? 1.0f / cn : 0.0f;
-#pragma unroll
-    for (int k = 0; k < kMlpIn; ++k)
-      xs[lane * kMlpIn + k] = k < K ? bf16_bits(sqrtf(sy.mu[k]) * c[k] * inv) : (unsigned short)0;
+    put_features<2>(xs, lane, [&](int k) { return k < K ? bf16_bits(sqrtf(sy.mu[k]) * c[k] * inv) : (unsigned short)0; });
     wave_lds_sync();
     float y0, y1, y2;
     mlp_forward_w(xs, net, lane, y0, y1, y2);
@@ -1084,8 +1077,11 @@ __global__ __launch_bounds__(64 * kLearnedWaves) void k_learned(ExtractArgs a) {
       }
     }
     wave_lds_sync();   // xs is rewritten by the next group
-#pragma unroll
-    for (int k = 0; k < K; ++k) c[k] = cx[k];
+    const size_t gn = gi + gstride;
+    if (gn < n_groups) {
+      const size_t vn = gn * 64 + lane;
+      load_raw<N>(a, vn < a.plane ? vn : a.plane - 1, c);
+    }
   }
   if (a.counters) {
     count_add(a.counters + 1, n_newton);

@@ -718,7 +718,7 @@ __global__ __launch_bounds__(64 * kLearnedWaves4) void k_learned4(ExtractArgs a)
   __shared__ float st[64 * 4];
   __shared__ float mono[64 * K];
   __shared__ __align__(16) unsigned char pk[Lay::packed];
-  __shared__ unsigned short xs_all[kLearnedWaves4][64 * kin];
+  __shared__ __align__(8) unsigned short xs_all[kLearnedWaves4][64 * kin];
   static_assert(Lay::packed % 16 == 0, "packed network copied in 16-byte pieces");
   for (int i = threadIdx.x; i < a.n_starts * 4; i += blockDim.x) st[i] = a.starts[i];
   for (int i = threadIdx.x; i < Lay::packed / 16; i += blockDim.x)
@@ -752,9 +752,7 @@ __global__ __launch_bounds__(64 * kLearnedWaves4) void k_learned4(ExtractArgs a)
     const size_t o = rv.o;
     if ((a.mode & 1) && active && rv.score) rv.score[o] = cn;
     const float inv = cn > 0.0f ? 1.0f / cn : 0.0f;
-    for (int k = 0; k < kin; ++k) xs[lane * kin + k] = 0;
-#pragma unroll
-    for (int k = 0; k < K; ++k) xs[lane * kin + k] = bf16_bits(sqrtf(sy.mu[k]) * c[k] * inv);
+    put_features<KT>(xs, lane, [&](int k) { return k < K ? bf16_bits(sqrtf(sy.mu[k]) * c[k] * inv) : (unsigned short)0; });
     wave_lds_sync();
     float y[4];
     mlp_forward_t<KT>(xs, net, lane, y);

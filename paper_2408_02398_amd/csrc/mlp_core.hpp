@@ -192,79 +192,92 @@ __device__ __forceinline__ bf16x4 relu_bf16_w(const f32x4& acc, const W& w, int 
   return h;
 }
 
+// Features of one wavefront's 64 voxels in LDS: [64][16 KT] bf16 in groups of 4,
+// the groups of a row permuted by the row where a row is 16 banks long (KT = 2):
+// rows 4 apart start in the same bank, and both a group written by all 64 lanes and
+// the 4 groups of 16 rows that a fragment read takes then meet each bank twice.
+// (In plain order with 2-byte accesses, half of the conflicts of a learned start.)
+template <int KT>
+__device__ __forceinline__ int xs_group(int row, int g) {
+  return row * 4 * KT + (KT == 2 ? g ^ ((row & 4) | (row >> 3 & 3)) : g);
+}
+
+// The calling lane's features f(k), k = 0 .. 16 KT - 1, as bf16 bits.
+template <int KT, class F>
+__device__ __forceinline__ void put_features(unsigned short* xs, int lane, F f) {
+#pragma unroll
+  for (int g = 0; g < 4 * KT; ++g) {
+    const bf16x4 v = {(short)f(4 * g), (short)f(4 * g + 1), (short)f(4 * g + 2), (short)f(4 * g + 3)};
+    *reinterpret_cast<bf16x4*>(xs + 4 * xs_group<KT>(lane, g)) = v;
+  }
+}
+
 // Forward pass of one wavefront's 64 voxels (voxel = lane), weights from w,
 // for a network of KT input tiles.
-//   xs: this wavefront's [64][16 KT] bf16 features in LDS, written by the
-//       lanes and made visible to the wavefront before the call.
+//   xs: this wavefront's features in LDS (put_features), 8-byte aligned and made
+//       visible to the wavefront before the call.
 // Returns y[0..3] (the first four outputs) of the calling lane's voxel.
 template <int KT, class W>
 __device__ __forceinline__ void mlp_forward_t(const unsigned short* xs, const W& w, int lane,
                                               float (&y)[4]) {
-  constexpr int kin = 16 * KT;
   const int r16 = lane & 15, q = lane >> 4;
-  // B fragments of X^T: lane L holds x[voxel 16 nt + L % 16][feature 16 s + 4 (L/16) + j]
-  bf16x4 xb[KT][4];
 #pragma unroll
-  for (int s = 0; s < KT; ++s)
+  for (int i = 0; i < 4; ++i) y[i] = 0.0f;
+  // two tiles of 16 voxels at a time: all four would hold twice the registers
+#pragma unroll 1
+  for (int n0 = 0; n0 < 4; n0 += 2) {
+    asm volatile("" ::: "memory");   // the weights stay in LDS between the passes
+    // B fragments of X^T: lane L holds x[voxel 16 nt + L % 16][feature 16 s + 4 (L/16) + j]
+    bf16x4 xb[KT][2];
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
+    for (int s = 0; s < KT; ++s)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) xb[s][nt][j] = (short)xs[(16 * nt + r16) * kin + 16 * s + 4 * q + j];
-  // layer 1: H1^T (64 x 64) = W1^T (64 x 16 KT) X^T (16 KT x 64)
-  bf16x4 h1[4][4];
+      for (int nt = 0; nt < 2; ++nt)
+        xb[s][nt] = *reinterpret_cast<const bf16x4*>(xs + 4 * xs_group<KT>(16 * (n0 + nt) + r16, 4 * s + q));
+    // layer 1: H1^T (64 x 32) = W1^T (64 x 16 KT) X^T (16 KT x 32)
+    bf16x4 h1[4][2];
 #pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    bf16x4 a[KT];
+    for (int m = 0; m < 4; ++m) {
+      bf16x4 a[KT];
 #pragma unroll
-    for (int s = 0; s < KT; ++s) a[s] = w.w1(4 * s + m);
+      for (int s = 0; s < KT; ++s) a[s] = w.w1(4 * s + m);
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
+      for (int nt = 0; nt < 2; ++nt) {
+        f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < KT; ++s) acc = mfma16(a[s], xb[s][nt], acc);
+        h1[m][nt] = relu_bf16_w(acc, w, 1, m);
+      }
+    }
+    // layer 2: H2^T = W2^T H1^T
+    bf16x4 h2[4][2];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      bf16x4 a[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) a[s] = w.w2(s * 4 + m);
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt) {
+        f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < 4; ++s) acc = mfma16(a[s], h1[s][nt], acc);
+        h2[m][nt] = relu_bf16_w(acc, w, 2, m);
+      }
+    }
+    // layer 3: Y^T (16 x 32) = W3^T H2^T; lanes 0..15 hold rows 0..3 (outputs)
+    // of voxel columns 16 nt + lane, and each voxel lane fetches its outputs from
+    // lane (voxel % 16) of tile voxel / 16
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) {
       f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int s = 0; s < KT; ++s) acc = mfma16(a[s], xb[s][nt], acc);
-      h1[m][nt] = relu_bf16_w(acc, w, 1, m);
+      for (int s = 0; s < 4; ++s) acc = mfma16(w.w3(s), h2[s][nt], acc);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float t = __shfl(acc[i] + w.b3(i), r16);
+        y[i] = q == n0 + nt ? t : y[i];
+      }
     }
-  }
-  // layer 2: H2^T = W2^T H1^T
-  bf16x4 h2[4][4];
-#pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    bf16x4 a[4];
-#pragma unroll
-    for (int s = 0; s < 4; ++s) a[s] = w.w2(s * 4 + m);
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int s = 0; s < 4; ++s) acc = mfma16(a[s], h1[s][nt], acc);
-      h2[m][nt] = relu_bf16_w(acc, w, 2, m);
-    }
-  }
-  // layer 3: Y^T (16 x 64) = W3^T H2^T; lanes 0..15 hold rows 0..3 (outputs)
-  // of voxel columns 16 nt + lane
-  bf16x4 a3[4];
-#pragma unroll
-  for (int s = 0; s < 4; ++s) a3[s] = w.w3(s);
-  float yv[4][4];
-#pragma unroll
-  for (int nt = 0; nt < 4; ++nt) {
-    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s = 0; s < 4; ++s) acc = mfma16(a3[s], h2[s][nt], acc);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) yv[i][nt] = acc[i] + w.b3(i);
-  }
-  // each voxel lane fetches its outputs from lane (voxel % 16) of tile voxel / 16
-  const int src = lane & 15, tile = lane >> 4;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    float pick = 0.0f;
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      const float t = __shfl(yv[i][nt], src);
-      pick = (tile == nt) ? t : pick;
-    }
-    y[i] = pick;
   }
 }
 
