@@ -59,12 +59,14 @@ __device__ __forceinline__ void wave_sync() {
 // Pooled workgroups for so many runs.  A run of max_iter updates is a serial chain,
 // and it advances at its wavefront's share of the SIMD: few runs end soonest with one
 // wavefront per SIMD (a workgroup per CU), many with all that fit.  Score and
-// orientation of e^3 voxels of degree 4 with 256 / 512 / 1024 / 2048 workgroups:
-// e = 24 (220 000 runs) 226 / 270 / 390 / 419 us, e = 32 (520 000) 322 / 291 / 419 /
-// 646, e = 48 (1.8 million) 725 / 475 / 447 / 593, e = 80 (8.2 million) 2625 / 1578 /
-// 1170 / 1110; degree 6 changes at the same counts.
+// orientation of e^3 voxels of degree 4 with 256 / 512 / 768 / 1024 / 2048 workgroups:
+// e = 24 (220 000 runs) 226 / 270 / 286 / 390 / 419 us, e = 32 (520 000) 322 / 291 /
+// 335 / 419 / 646, e = 40 (1.0 million) - / - / 355 / 418 / -, e = 48 (1.8 million)
+// 725 / 475 / 422 / 447 / 593, e = 64 (4.2 million) 1431 / 866 / 725 /
+// 673 / 690, e = 80 (8.2 million) 2625 / 1578 / - / 1170 / 1110; degree 6 changes at
+// the same counts.
 __host__ __device__ inline unsigned pool_groups(size_t runs) {
-  return runs < 350000 ? 256 : runs < 1000000 ? 512 : runs < 4000000 ? 1024 : 2048;
+  return runs < 350000 ? 256 : runs < 750000 ? 512 : runs < 2000000 ? 768 : runs < 4000000 ? 1024 : 2048;
 }
 
 }  // namespace ttm
