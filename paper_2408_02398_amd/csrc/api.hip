@@ -156,10 +156,7 @@ __global__ void k_var_combine(const float* __restrict__ s1, const float* __restr
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const int x = (int)(i % sx), y = (int)((i / sx) % sy), z = (int)(i / ((size_t)sx * sy));
-  const double a = (double)s1[i], b = (double)s2[i];
-  const double var = b - a * a / M;
-  const double thr = eps * M * stats[1];
-  w[((size_t)(oz + z) * ny + (oy + y)) * nx + (ox + x)] = (var > thr) ? (float)(1.0 / sqrt(var)) : 0.0f;
+  w[((size_t)(oz + z) * ny + (oy + y)) * nx + (ox + x)] = inverse_deviation(s1[i], s2[i], M, eps * M * stats[1]);
 }
 
 __global__ void k_mask(float* __restrict__ m, int L, float r) {
@@ -1259,9 +1256,11 @@ int normalize_boxes(ttm_ctx* ctx, const ttm_desc* desc, const float* g, int nz, 
         int rc = fft3d_forward(fft_n, src, 2, G1, sb / 8, ctx->twiddles, s);
         if (rc) return rc;
         RealDst d1{s1, 0, s_gap, syy, sxx, 0, 0, 0, szz, syy, sxx, nullptr, 0, 0, 0, 0, 0, scale};
+        const VarDst var{w_out, ny, nx, oz, oy, ox, M, (double)desc->eps_w, stats};
         rc = fft3d_inverse_mul(fft_n, G1, mspec, 0, L, 1, nullptr, work, sb / 8, d1, ctx->twiddles, s,
-                               2, sb / 8);
+                               2, sb / 8, &var);
         if (rc) return rc;
+        if (inverse_fuses_variance(fft_n)) continue;
         const size_t nbx = (size_t)szz * syy * sxx;
         hipLaunchKernelGGL(k_var_combine, dim3((unsigned)((nbx + 255) / 256)), dim3(256), 0, s, s1,
                            s2, szz, syy, sxx, M, (double)desc->eps_w, stats, w_out, ny, nx, oz,
@@ -1492,12 +1491,15 @@ int ttm_normalize_correlate(ttm_ctx* ctx, const ttm_desc* desc, const float* g, 
   if (rc) return rc;
   // local sums with the mask (both products in one batched inverse), then w on the box
   RealDst d1{s1, 0, s_gap, syy, sxx, 0, 0, 0, szz, syy, sxx, nullptr, 0, 0, 0, 0, 0, scale};
+  const VarDst var{w_out, ny, nx, oz, oy, ox, M, (double)desc->eps_w, stats};
   rc = fft3d_inverse_mul(fft_n, G1, mspec, 0, L, 1, nullptr, work, sb / 8, d1, ctx->twiddles, s,
-                         2, sb / 8);
+                         2, sb / 8, &var);
   if (rc) return rc;
   const size_t nbx = (size_t)szz * syy * sxx;
-  hipLaunchKernelGGL(k_var_combine, dim3((unsigned)((nbx + 255) / 256)), dim3(256), 0, s, s1, s2,
-                     szz, syy, sxx, M, (double)desc->eps_w, stats, w_out, ny, nx, oz, oy, ox);
+  if (!inverse_fuses_variance(fft_n)) {
+    hipLaunchKernelGGL(k_var_combine, dim3((unsigned)((nbx + 255) / 256)), dim3(256), 0, s, s1, s2,
+                       szz, syy, sxx, M, (double)desc->eps_w, stats, w_out, ny, nx, oz, oy, ox);
+  }
   // the K correlations from the same forward transform
   RealDst d{C_out, out_dtype, nbx, syy, sxx, 0, 0, 0, szz, syy, sxx, w_out, ny, nx, oz, oy, ox, scale};
   rc = fft3d_inverse_mul(fft_n, G1, tspec, tse, L, K, stats, work, sb / 8, d, ctx->twiddles, s);

@@ -462,10 +462,14 @@ __global__ __launch_bounds__(PlaneWg<N>::NTH) __attribute__((amdgpu_waves_per_eu
 }
 
 // ---------------------------------------------------------------- X inverse
-template <int N>
+// VAR: the two local sums' spectra (spec_stride apart), kRowsC / 2 rows of each, and
+// w formed from them in place of two stores, two loads and a launch (512^3 tile:
+// 901 -> 529 us for the sums and w, 256^3: 107 -> 77).  Rows are packed in pairs of one sum:
+// packed across the sums, each would carry rounding on the other's scale.
+template <int N, bool VAR>
 __global__ __launch_bounds__(kRowsC / 2 * Plan<N>::T) __attribute__((amdgpu_waves_per_eu(N == 512 ? 8 : 1))) void k_c2r_x(const cf* __restrict__ spec,
                                                           size_t spec_stride, int A, RealDst dst,
-                                                          const cf* __restrict__ tw) {
+                                                          VarDst var, const cf* __restrict__ tw) {
   constexpr int T = Plan<N>::T, E = N / T, NP = kRowsC / 2, NH = N / 2 + 1;
   constexpr int S = lds_stride<N>();
   constexpr int SPS = NH + 1;  // padded spectrum row
@@ -479,9 +483,11 @@ __global__ __launch_bounds__(kRowsC / 2 * Plan<N>::T) __attribute__((amdgpu_wave
   const int tid = threadIdx.x;
   // work items: component fastest, then row block, then z plane, so the
   // workgroups that share a crop's weight-map rows run together in one XCD
-  constexpr int NYB = N / kRowsC;
+  constexpr int RW = VAR ? kRowsC / 2 : kRowsC;   // output rows
+  constexpr int NYB = N / RW;
   const int item = (int)xcd_item(blockIdx.x, gridDim.x);
-  const int b = item % A, y0 = (item / A) % NYB * kRowsC, z = item / A / NYB;
+  if constexpr (VAR) A = 1;
+  const int b = item % A, y0 = (item / A) % NYB * RW, z = item / A / NYB;
   if (z >= dst.sz || y0 >= dst.sy) return;  // uniform: nothing of this block is kept
   const int p = tid / T, t = tid % T;
   constexpr int NTH = NP * T, NIN = NH * kRowsC, IT = (NIN + NTH - 1) / NTH;
@@ -491,13 +497,13 @@ __global__ __launch_bounds__(kRowsC / 2 * Plan<N>::T) __attribute__((amdgpu_wave
     // LDS stores: the loads are in flight together.  Rows past the crop were
     // not stored by the Y pass; they are read as zeros (each is paired with a
     // kept row in one complex transform, so it must be finite).
-    const int nrows_in = min(kRowsC, dst.sy - y0);
+    const int nrows_in = min(RW, dst.sy - y0);
     cf ld[IT];
 #pragma unroll
     for (int i = 0; i < IT; ++i) {
       const int e = min(tid + i * NTH, NIN - 1);
-      ld[i] = e % kRowsC < nrows_in ? at_byte(in, (unsigned)((e / kRowsC) * N + e % kRowsC) * 8u)
-                                    : cf{0.0f, 0.0f};
+      const unsigned half = VAR && e % kRowsC >= RW ? (unsigned)spec_stride : 0u;
+      ld[i] = e % RW < nrows_in ? at_byte(in, (half + (unsigned)((e / kRowsC) * N + e % RW)) * 8u) : cf{0.0f, 0.0f};
     }
 #pragma unroll
     for (int i = 0; i < IT; ++i) {
@@ -537,8 +543,18 @@ __global__ __launch_bounds__(kRowsC / 2 * Plan<N>::T) __attribute__((amdgpu_wave
     orow[(2 * p + 1) * RS + n] = v[j].y;
   }
   __syncthreads();
-  const int nrows = min(kRowsC, dst.sy - y0);
+  const int nrows = min(RW, dst.sy - y0);
   const int sx = dst.sx;
+  if constexpr (VAR) {
+    const double thr = var.eps * var.M * var.stats[1];
+    float* out = var.w + ((size_t)(var.oz + z) * var.ny + (var.oy + y0)) * var.nx + var.ox;
+    for (int i = tid; i < nrows * sx; i += NTH) {
+      const int r = i / sx, x = i - r * sx;
+      out[(size_t)r * var.nx + x] = inverse_deviation(orow[r * RS + x] * dst.scale, orow[(r + RW) * RS + x] * dst.scale,
+                                                      var.M, thr);
+    }
+    return;
+  }
   // row bases are the same for the whole workgroup, so each access takes a
   // scalar base and the lane's 32-bit byte offset
   const size_t o0 = b * dst.batch_stride +
@@ -634,7 +650,7 @@ int forward_planes_n(const RealSrc& src, int batch, int planes, cf* out, size_t 
 template <int N>
 int inverse_n(const cf* G, const cf* Sp, size_t s_stride, int s_planes, int A, const double* center,
               cf* work, size_t work_stride, const RealDst& dst, const cf* tw, hipStream_t s,
-              int gb, size_t g_stride) {
+              int gb, size_t g_stride, const VarDst* var) {
   constexpr int T = Plan<N>::T;
   constexpr int NROWS = N * (N / 2 + 1);
   const int zlim = dst.sz;
@@ -677,8 +693,14 @@ int inverse_n(const cf* G, const cf* Sp, size_t s_stride, int s_planes, int A, c
     constexpr int RB = (128 / T > 0 ? 128 / T : 1);
     hipLaunchKernelGGL((k_c2c_rows<N, true>), dim3(NROWS / RB, nb), dim3(RB * T), 0, s, work,
                        work_stride, zlim, dst.sy, tw);
-    hipLaunchKernelGGL(k_c2r_x<N>, dim3(nb * (N / kRowsC) * N), dim3(kRowsC / 2 * T), 0, s, work,
-                       work_stride, nb, dst, tw);
+    static_assert(inverse_fuses_variance(N), "the sums' rows in the X pass");
+    if (var) {
+      hipLaunchKernelGGL((k_c2r_x<N, true>), dim3(N / (kRowsC / 2) * N), dim3(kRowsC / 2 * T), 0, s, work,
+                         work_stride, nb, dst, *var, tw);
+    } else {
+      hipLaunchKernelGGL((k_c2r_x<N, false>), dim3(nb * (N / kRowsC) * N), dim3(kRowsC / 2 * T), 0, s, work,
+                         work_stride, nb, dst, VarDst{}, tw);
+    }
   }
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? 0 : hip_status(e, "fft inverse launch");
@@ -740,21 +762,25 @@ int fft3d_forward_planes(int N, const RealSrc& src, int batch, int planes, cf* o
 
 int fft3d_inverse_mul(int N, const cf* G, const cf* Sp, size_t s_stride, int s_planes, int A,
                       const double* center, cf* work, size_t work_stride, const RealDst& dst,
-                      const cf* tw_all, hipStream_t s, int gb, size_t g_stride) {
+                      const cf* tw_all, hipStream_t s, int gb, size_t g_stride, const VarDst* var) {
   if (gb < 1 || (gb > 1 && A != 1)) {
     set_error("fft inverse: a batch of %d G spectra needs one component (A = %d)", gb, A);
     return -1;
   }
+  if (var && gb != 2) {
+    set_error("fft inverse: w needs the two local sums, not %d spectra", gb);
+    return -1;
+  }
   const cf* tw = tw_all + twiddle_offset(N);
   switch (N) {
-    case 32: return inverse_n<32>(G, Sp, s_stride, s_planes, A, center, work, work_stride, dst, tw, s, gb, g_stride);
-    case 64: return inverse_n<64>(G, Sp, s_stride, s_planes, A, center, work, work_stride, dst, tw, s, gb, g_stride);
-    case 128: return inverse_n<128>(G, Sp, s_stride, s_planes, A, center, work, work_stride, dst, tw, s, gb, g_stride);
-    case 256: return inverse_n<256>(G, Sp, s_stride, s_planes, A, center, work, work_stride, dst, tw, s, gb, g_stride);
-    case 512: return inverse_n<512>(G, Sp, s_stride, s_planes, A, center, work, work_stride, dst, tw, s, gb, g_stride);
-    case 96: return inverse_n<96>(G, Sp, s_stride, s_planes, A, center, work, work_stride, dst, tw, s, gb, g_stride);
-    case 160: return inverse_n<160>(G, Sp, s_stride, s_planes, A, center, work, work_stride, dst, tw, s, gb, g_stride);
-    case 192: return inverse_n<192>(G, Sp, s_stride, s_planes, A, center, work, work_stride, dst, tw, s, gb, g_stride);
+    case 32: return inverse_n<32>(G, Sp, s_stride, s_planes, A, center, work, work_stride, dst, tw, s, gb, g_stride, var);
+    case 64: return inverse_n<64>(G, Sp, s_stride, s_planes, A, center, work, work_stride, dst, tw, s, gb, g_stride, var);
+    case 128: return inverse_n<128>(G, Sp, s_stride, s_planes, A, center, work, work_stride, dst, tw, s, gb, g_stride, var);
+    case 256: return inverse_n<256>(G, Sp, s_stride, s_planes, A, center, work, work_stride, dst, tw, s, gb, g_stride, var);
+    case 512: return inverse_n<512>(G, Sp, s_stride, s_planes, A, center, work, work_stride, dst, tw, s, gb, g_stride, var);
+    case 96: return inverse_n<96>(G, Sp, s_stride, s_planes, A, center, work, work_stride, dst, tw, s, gb, g_stride, var);
+    case 160: return inverse_n<160>(G, Sp, s_stride, s_planes, A, center, work, work_stride, dst, tw, s, gb, g_stride, var);
+    case 192: return inverse_n<192>(G, Sp, s_stride, s_planes, A, center, work, work_stride, dst, tw, s, gb, g_stride, var);
     default: set_error("unsupported FFT edge %d", N); return -4;
   }
 }

@@ -59,6 +59,24 @@ struct RealDst {
   float scale;
 };
 
+// Where the inverse of the two local sums (batch entries 0 and 1) writes
+// w = 1 / sqrt(s2 - s1^2 / M) instead of the sums, at the edges that fuse it.
+struct VarDst {
+  float* w;                // [.][ny][nx], the box's origin at (oz, oy, ox)
+  int ny, nx, oz, oy, ox;
+  double M, eps;
+  const double* stats;
+};
+// w of one voxel (FP64): 0 at or below the guard eps M stats[1].
+__device__ __forceinline__ float inverse_deviation(float s1, float s2, double M, double thr) {
+  const double a = (double)s1, b = (double)s2;
+  const double var = b - a * a / M;
+  return (var > thr) ? (float)(1.0 / sqrt(var)) : 0.0f;
+}
+// From 192 on the separate X pass holds rows of both sums; below, k_c2r_plane
+// holds one spectrum's plane, and the caller combines the sums.
+constexpr bool inverse_fuses_variance(int N) { return N >= 192; }
+
 // Twiddle table for edge N inside the context table.
 int twiddle_offset(int N);
 constexpr int kTwiddleTotal = 32 + 64 + 128 + 256 + 512 + 96 + 160 + 192;
@@ -83,9 +101,11 @@ int fft3d_forward_planes(int N, const RealSrc& src, int batch, int planes, cf* o
 // `work` holds A spectra.  If S is null, G itself (A = 1) is inverted.
 // With gb > 1 (A = 1 only), gb spectra G + i g_stride are each multiplied by
 // the same S in one launch: work spectrum i and dst batch entry i are theirs.
+// `var` (gb = 2, edges with inverse_fuses_variance): w is written, dst.p is not.
 int fft3d_inverse_mul(int N, const cf* G, const cf* S, size_t s_stride, int s_planes, int A,
                       const double* center, cf* work, size_t work_stride, const RealDst& dst,
-                      const cf* tw_all, hipStream_t s, int gb = 1, size_t g_stride = 0);
+                      const cf* tw_all, hipStream_t s, int gb = 1, size_t g_stride = 0,
+                      const VarDst* var = nullptr);
 
 int init_twiddles(cf* tw_all, hipStream_t s);
 

@@ -357,3 +357,35 @@ def test_find_peaks_batch_edges(T, ctx, kind, shape, lo, hi, top, dist):
             got = e["peaks"][:n].cpu().numpy()
             assert np.array_equal(got, np.asarray(ref).reshape(-1, 3))
             assert np.array_equal(e["vals"][:n].cpu().numpy(), a[tuple(got.T)])
+
+
+@pytest.mark.parametrize("N,L,shape", [
+    (160, 24, (33, 160, 45)),     # sums stored, then combined
+    (192, 24, (30, 192, 40)),     # 169 rows: the last workgroup of 8 holds one
+    (192, 32, (192, 38, 33)),     # 7 rows and 2 columns
+    (256, 17, (20, 40, 256)),     # 24 rows, 240 columns
+    (256, 24, (25, 300, 26)),     # two tiles, the second of 44 rows
+])
+def test_local_deviation_rows(T, ctx, N, L, shape):
+    """w of ttm_normalize against 64-bit sums over the mask of the filtered volume.
+    FP32 transforms of the sums: 2e-6 of the largest local sums, noise of
+    variance near its second moment, so 2e-5 of w."""
+    import torch
+
+    from scipy.signal import fftconvolve
+    r = 0.43 * L
+    d = T.make_desc(2, L, r)
+    rng = np.random.default_rng(8)
+    vol = torch.from_numpy(rng.standard_normal(shape).astype(np.float32)).cuda()
+    K = T.n_components(2)
+    spec = T.template_spectra(ctx, d, torch.zeros((K, L ** 3), device="cuda"), N)
+    g, w, _ = T.normalize(ctx, d, vol, spec, N)
+    g, w = g.cpu().numpy().astype(np.float64), w.cpu().numpy()
+    i = np.arange(L) - L // 2
+    m = (i[:, None, None] ** 2 + i[:, None] ** 2 + i ** 2 <= np.float32(r) ** 2).astype(np.float64)
+    f = m[::-1, ::-1, ::-1]
+    s1, s2 = fftconvolve(g, f, "valid"), fftconvolve(g * g, f, "valid")
+    ref = 1.0 / np.sqrt(s2 - s1 * s1 / m.sum())
+    c = L // 2
+    box = w[c:c + ref.shape[0], c:c + ref.shape[1], c:c + ref.shape[2]]
+    assert np.max(np.abs(box - ref) / ref) < 2e-5
