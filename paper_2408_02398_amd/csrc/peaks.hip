@@ -1132,6 +1132,7 @@ int find_peaks(const float* score, int nz, int ny, int nx, const int32_t lo[3],
       }
     }
     hipLaunchKernelGGL(k_compact, cgrid, dim3(256), 0, s, score, r, &pick->key_lo, keys_a, &pick->count);
+    TTM_HIP(hipGetLastError());   // a launch that failed leaves counts that mean nothing
     TTM_HIP(hipMemcpyAsync(&got, pick, sizeof(Pick), hipMemcpyDeviceToHost, s));
     TTM_HIP(hipStreamSynchronize(s));
     const int64_t m = got.count;
@@ -1161,6 +1162,7 @@ int find_peaks(const float* score, int nz, int ny, int nx, const int32_t lo[3],
           hipLaunchKernelGGL(k_rank, dim3(kKeptMax / 64), dim3(256), 0, s, st.kept, pick, ny, nx, top_p,
                              peaks_out, vals_out);
         }
+        TTM_HIP(hipGetLastError());
         TTM_HIP(hipMemcpyAsync(&got, pick, sizeof(Pick), hipMemcpyDeviceToHost, s));
         TTM_HIP(hipStreamSynchronize(s));
       }
