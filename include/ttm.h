@@ -76,7 +76,8 @@ typedef enum {
   TTM_OP_CORRELATE = 3,
   TTM_OP_PEAKS = 4,
   TTM_OP_EXTRACT = 5,     /* nz x ny x nx = the extraction box            */
-  TTM_OP_MLP_TRAIN = 6,   /* nz = batch size, ny = nx = 1                 */
+  TTM_OP_MLP_TRAIN = 6,   /* nz = batch size, ny = nx = 1 (the size covers
+                             every smaller batch)                        */
   TTM_OP_PREFILTER = 7,   /* nz x ny x nx = the volume (fft_n unused)     */
   TTM_OP_REFINE = 8,      /* nz = peaks, ny = the refinement radius r_s
                              rounded up (the size covers every smaller r_s) */

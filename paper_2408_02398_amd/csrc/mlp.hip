@@ -16,6 +16,8 @@
 // backward pass and writes its share of the gradients, k_train_update adds the
 // shares in order and updates.  Every product runs on BF16 matrix-core tiles
 // (operands rounded to BF16, FP32 accumulation).
+#include <algorithm>
+
 #include "internal.hpp"
 #include "mlp_core.hpp"
 #include "sym_tables.hpp"
@@ -437,8 +439,11 @@ __global__ void k_pack(const float* __restrict__ p, MlpRt r, unsigned char* __re
 }  // namespace
 
 size_t mlp_train_workspace(int B) {
-  // gradient shares and loss sums of the workgroups
-  return (size_t)train_groups(B) * (MlpLayout<3>::params + 1) * 4;
+  // gradient shares and loss sums of the workgroups: as many as any batch of up to B
+  // samples has (a batch just over a multiple of kTrainBlock * kTrainGroups has fewer
+  // than one just under it)
+  const size_t most = std::min((size_t)kTrainGroups, ((size_t)B + kTrainBlock - 1) / kTrainBlock);
+  return most * (MlpLayout<3>::params + 1) * 4;
 }
 
 int mlp_train_step(int degree, int dprime, const float* Cin, const float* T, int B, float* params,
