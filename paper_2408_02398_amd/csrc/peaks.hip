@@ -11,13 +11,15 @@
 //      levels, picks a threshold that about `want` voxels pass,
 //   2. the voxels that pass are compacted as 64-bit keys (~score_bits << 32 |
 //      linear index), so ascending key order is exactly the visiting order,
-//   3. the candidates settle in parallel (k_settle): one is kept once every
-//      higher-ranked candidate within D is dropped, and dropped once one of them
-//      is kept -- the sequential walk's answer,
+//   3. of a short list the smallest key is kept and drops those within D, again and
+//      again (k_short); the candidates of a longer one settle in parallel
+//      (k_settle): one is kept once every higher-ranked candidate within D is
+//      dropped, and dropped once one of them is kept -- the sequential walk's answer,
 //   4. the kept ones are ranked among each other and the first P written.
 // If fewer than P peaks are found while lower-ranked voxels remain, `want` is
-// raised and the search repeats.  Too many or too dense candidates for step 3, and the
-// search whose count stays on the device, take a sorted walk instead:
+// raised and the search repeats.  Lists that step 3 does not settle in a few rounds,
+// second searches, and the search whose count stays on the device take a sorted walk
+// instead:
 //   * LSD radix sort of the keys (8-bit digits, stable ranks from wavefront
 //     ballots),
 //   * one workgroup walks the sorted keys in chunks of 1024: every lane
@@ -62,13 +64,14 @@ constexpr int kHistRows = 32;
 // What the threshold search leaves on the device.
 struct Pick {
   unsigned top;       // coarse bin
+  unsigned most;      // the highest coarse bin that is not empty
   unsigned above;     // sampled voxels in the bins over it
   unsigned key_lo;    // candidates: score bits >= key_lo
   unsigned count;     // candidates
   unsigned undecided, kept;
   int n_found;
-  unsigned pad;
-  unsigned long long pairs;   // (candidate, neighbour) pairs the settling may look at
+  unsigned open;              // candidates that k_drop left undecided
+  unsigned long long work;    // candidates in the 27 cells around each of those, added up
 };
 
 __global__ __launch_bounds__(256) void k_hist(const float* __restrict__ score, Region r, int level,
@@ -121,7 +124,7 @@ __global__ __launch_bounds__(256) void k_hist(const float* __restrict__ score, R
 }
 
 // One workgroup: the bin in which the histogram, summed from the top, reaches
-// `want` sampled voxels.  Level 0 leaves the coarse bin and the sum over it, level 1
+// `want` sampled voxels.  Level 0 leaves the coarse bin, the sum over it and the highest bin in use, level 1
 // the threshold (key_lo stays 0, every voxel, when all bins together stay below
 // `want`).
 __global__ __launch_bounds__(1024) void k_pick(const unsigned* __restrict__ hist, int level, unsigned want, Pick* pick) {
@@ -147,6 +150,7 @@ __global__ __launch_bounds__(1024) void k_pick(const unsigned* __restrict__ hist
   if (none || run >= want) return;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
+    if (level == 0 && run == 0 && v[i]) pick->most = kHistBins - 1 - (4 * t + i);
     if (run < want && run + v[i] >= want) {
       const unsigned bin = kHistBins - 1 - (4 * t + i);
       if (level == 0) {
@@ -166,7 +170,7 @@ __global__ __launch_bounds__(1024) void k_pick(const unsigned* __restrict__ hist
 // kCompactList go out by themselves), so a workgroup reserves its slots with one
 // atomic: the counter is one address for the whole chip, and an atomic for each 64
 // voxels with a key in them bound this at 465 us for 131 000 keys of
-// 512 x 512 x 928 (now 280 us, the map read once).
+// 512 x 928 x 928 (now 280 us, the map read once).
 constexpr int kCompactRows = 16, kCompactList = 1024;
 __global__ __launch_bounds__(256) void k_compact(const float* __restrict__ score, Region r,
                                                  const unsigned* __restrict__ key_lo_at,
@@ -333,17 +337,25 @@ __global__ __launch_bounds__(kSortBlock) void k_rs_scatter(
 // ---------------------------------------------------------------- settling
 // Candidates in the order of the exclusion grid's cells (edge >= D): those within
 // D of one lie in the 27 cells around its own, which are nine runs of the list.
-// A short list (up to kFlatMax) is one cell.
 constexpr unsigned kSettleMax = 1u << 20;   // candidates
-constexpr unsigned kFlatMax = 4096;
 constexpr unsigned kKeptMax = 16384;        // kept ones
-constexpr int kSettleRounds = 6;            // between two looks at what is left (random maps take about 11)
+constexpr int kSettleRounds = 6;            // between two looks at what is left (random maps take about 8)
 constexpr int kSettleLooks = 32;            // then the sorted walk
-// Pairs up to which the candidates settle in parallel.  Where candidates fill the
-// map (a peak count out of reach makes every voxel one) each would look at every
-// voxel of 27 cells; the sorted walk tests a key against the few kept peaks of
-// those cells instead.
-constexpr unsigned long long kSettlePairs = 1ull << 29;
+constexpr unsigned kSettlePer = 16;         // candidates of a wavefront in a round, few of them open
+
+// Whether the rounds (k_settle) pay, with `open` of m candidates left by k_drop: else
+// the sorted walk takes over.  They settle in a few rounds what lies on the slopes
+// of peaks or is noise (open / m up to 0.35), and one peak a round along a ramp, a
+// ridge or a plateau (0.72 to 1.0); and a round reads every candidate in reach of an
+// open one, where the walk reads only kept peaks.  The whole search with rounds against
+// with the walk: noise 256^3, 2000 peaks 0.98 / 3.1 ms; ridges 200 x 200 x 400, 2000
+// peaks 13.8 / 2.7; equal scores 64^3, 2000 peaks 46 / 2.9; maxima of sigma 9 in 192^3, 30
+// peaks 2.9 / 0.78, in 256^3, 30 peaks 2.1 / 0.83.
+constexpr unsigned kSettleNear = 2048;      // neighbours of an open candidate, on average
+constexpr unsigned long long kSettleWork = 1ull << 27;
+__host__ __device__ inline bool rounds_pay(const Pick& p, unsigned m) {
+  return 2ull * p.open <= m && p.work <= kSettleWork && p.work <= (unsigned long long)kSettleNear * p.open;
+}
 
 struct Settle {
   const unsigned long long* in;   // keys as compacted
@@ -352,11 +364,9 @@ struct Settle {
   int* state;                     // 0 undecided, 1 kept, 2 dropped
   unsigned* start;                // first candidate of each cell, ncell + 1
   unsigned* fill;                 // candidates placed per cell
-  unsigned long long* best;       // smallest key of each cell
+  unsigned long long* best;       // ~(smallest key) of each cell, 0: none
   ushort4* lead;                  // its place and w = 1 where it is kept at once
   unsigned m;
-  int flat;
-  unsigned per;                   // candidates of a wavefront in a round
   int ny, nx;
   float d2, cell;
   int gz, gy, gx;
@@ -374,65 +384,76 @@ __device__ __forceinline__ int cell_of(const Settle& s, const ushort4& p) {
 }
 
 // Candidates per cell (cleared before), then, with the cells' starts known, the
-// candidates in cell order (in any order within a cell).
+// candidates in cell order (in any order within a cell).  The list comes in pieces of
+// rows, so neighbouring lanes mostly share a cell: a run of them adds with one atomic
+// (with one a lane, those of a wavefront queue for one address: 0.4 to 0.8 ms for
+// 260 000 to 880 000 candidates of 64^3 and 96^3 maps).
 template <bool SCATTER>
 __global__ __launch_bounds__(256) void k_cells(Settle s) {
   const unsigned i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= s.m) return;
-  const unsigned long long key = s.in[i];
+  const int lane = threadIdx.x & 63;
+  const unsigned long long key = i < s.m ? s.in[i] : ~0ull;
   const ushort4 p = key_pos(key, s.ny, s.nx);
-  if (!SCATTER) {
-    atomicAdd(&s.start[cell_of(s, p)], 1u);
+  const int c = i < s.m ? cell_of(s, p) : -1;
+  const int before = __shfl_up(c, 1);
+  const bool head = lane == 0 || before != c;
+  const unsigned long long heads = __ballot(head);
+  const int first = 63 - __clzll((long long)(heads & (~0ull >> (63 - lane))));
+  const unsigned long long rest = lane == 63 ? 0ull : heads >> (lane + 1);
+  const int next = rest ? lane + __ffsll((long long)rest) : 64;   // this run: lanes first .. next - 1
+  if constexpr (!SCATTER) {
+    if (head && c >= 0) atomicAdd(&s.start[c], (unsigned)(next - first));
   } else {
-    unsigned at = i;
-    if (!s.flat) {
-      const int c = cell_of(s, p);
-      at = s.start[c] + atomicAdd(&s.fill[c], 1u);
-      atomicMin(&s.best[c], key);
+    unsigned long long low = key;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const unsigned long long o = __shfl_down(low, off);
+      if (lane + off < next && o < low) low = o;
     }
+    unsigned base = 0;
+    if (head && c >= 0) {
+      base = s.start[c] + atomicAdd(&s.fill[c], (unsigned)(next - first));
+      atomicMax(&s.best[c], ~low);
+    }
+    const unsigned at = (unsigned)__shfl((int)base, first) + (unsigned)(lane - first);
+    if (i >= s.m) return;
     s.key[at] = key;
     s.pos[at] = p;
     s.state[at] = 0;
   }
 }
 
-// Pairs of the list: each cell's candidates times those of its 27 cells.
-__global__ __launch_bounds__(256) void k_pairs(Settle s) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  unsigned long long v = 0;
-  if (c < s.gz * s.gy * s.gx) {
-    const int x = c % s.gx, y = (c / s.gx) % s.gy, z = c / (s.gx * s.gy);
-    for (int o = 0; o < 9; ++o) {
-      const int z2 = z + o / 3 - 1, y2 = y + o % 3 - 1;
-      if (z2 < 0 || z2 >= s.gz || y2 < 0 || y2 >= s.gy) continue;
-      const int row = (z2 * s.gy + y2) * s.gx;
-      v += s.start[row + min(x + 1, s.gx - 1) + 1] - s.start[row + max(x - 1, 0)];
-    }
-    v *= s.start[c + 1] - s.start[c];
-    s.best[c] = ~0ull;
-  }
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off);
-  if ((threadIdx.x & 63) == 0 && v) atomicAdd(&s.pick->pairs, v);
-}
-
 // The cells' best candidates with nothing ranked higher within D: they are kept.
-// A wavefront per cell.
+// A wavefront per cell; cells around it whose best ranks lower hold nothing to look
+// at, and one with more than kLeadScan candidates to look at is left to the rounds.
+constexpr unsigned kLeadScan = 4096;
 __global__ __launch_bounds__(256) void k_lead(Settle s) {
   const int c = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const unsigned lane = threadIdx.x & 63;
-  if (c >= s.gz * s.gy * s.gx || s.pick->pairs > kSettlePairs) return;   // uniform per wavefront
+  const int lane = threadIdx.x & 63;
+  if (c >= s.gz * s.gy * s.gx) return;             // uniform per wavefront
   const int x = c % s.gx, y = (c / s.gx) % s.gy, z = c / (s.gx * s.gy);
-  const unsigned long long own = s.best[c];
+  const unsigned long long own = ~s.best[c];
   ushort4 p = key_pos(own, s.ny, s.nx);
-  bool lead = own != ~0ull;
-  for (int o = 0; o < 9 && lead; ++o) {
-    const int z2 = z + o / 3 - 1, y2 = y + o % 3 - 1;
-    if (z2 < 0 || z2 >= s.gz || y2 < 0 || y2 >= s.gy) continue;
-    const int row = (z2 * s.gy + y2) * s.gx;
-    const unsigned e = s.start[row + min(x + 1, s.gx - 1) + 1];
-    for (unsigned j = s.start[row + max(x - 1, 0)] + lane; __ballot(j < e) && lead; j += 64) {
+  // lane: one of the 27 cells
+  const int z2 = z + lane / 9 - 1, y2 = y + lane / 3 % 3 - 1, x2 = x + lane % 3 - 1;
+  unsigned b = 0, n = 0;
+  if (lane < 27 && z2 >= 0 && z2 < s.gz && y2 >= 0 && y2 < s.gy && x2 >= 0 && x2 < s.gx) {
+    const int c2 = (z2 * s.gy + y2) * s.gx + x2;
+    if (~s.best[c2] < own) {
+      b = s.start[c2];
+      n = s.start[c2 + 1] - b;
+    }
+  }
+  unsigned all = n;
+  for (int off = 32; off > 0; off >>= 1) all += (unsigned)__shfl_xor((int)all, off);
+  bool lead = own != ~0ull && all <= kLeadScan;
+  for (unsigned long long todo = __ballot(n > 0); todo && lead; todo &= todo - 1) {
+    const int o = __ffsll((long long)todo) - 1;
+    const unsigned b2 = (unsigned)__shfl((int)b, o), e2 = b2 + (unsigned)__shfl((int)n, o);
+    for (unsigned j0 = b2; j0 < e2 && lead; j0 += 64) {
+      const unsigned j = j0 + lane;
       bool above = false;
-      if (j < e && s.key[j] < own) {
+      if (j < e2 && s.key[j] < own) {
         const ushort4 q = s.pos[j];
         const float ddz = (float)((int)p.x - (int)q.x), ddy = (float)((int)p.y - (int)q.y),
                     ddx = (float)((int)p.z - (int)q.z);
@@ -447,46 +468,73 @@ __global__ __launch_bounds__(256) void k_lead(Settle s) {
 
 // A thread per candidate: kept when it leads its cell, dropped within D of a leader.
 // Most candidates of a map of peaks are on the slopes of a leader, and this spares
-// them the rounds below.
+// them the rounds below.  Those it leaves are counted, and the candidates around them.
 __global__ __launch_bounds__(256) void k_drop(Settle s) {
-  const unsigned i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= s.m || s.pick->pairs > kSettlePairs) return;
-  const ushort4 p = s.pos[i];
-  const int hz = (int)(p.x / s.cell), hy = (int)(p.y / s.cell), hx = (int)(p.z / s.cell);
-  int state = 0;
-#pragma unroll
-  for (int o = 0; o < 27; ++o) {
-    const int z2 = min(max(hz + o / 9 - 1, 0), s.gz - 1), y2 = min(max(hy + o / 3 % 3 - 1, 0), s.gy - 1),
-              x2 = min(max(hx + o % 3 - 1, 0), s.gx - 1);
-    const ushort4 q = s.lead[(z2 * s.gy + y2) * s.gx + x2];
-    const float ddz = (float)((int)p.x - (int)q.x), ddy = (float)((int)p.y - (int)q.y),
-                ddx = (float)((int)p.z - (int)q.z);
-    const float d2 = ddz * ddz + ddy * ddy + ddx * ddx;
-    if (q.w) state = d2 == 0.0f ? 1 : (d2 < s.d2 ? 2 : state);
+  __shared__ unsigned n_open;
+  __shared__ unsigned long long n_work;
+  if (threadIdx.x == 0) {
+    n_open = 0;
+    n_work = 0;
   }
-  s.state[i] = state;
+  __syncthreads();
+  const unsigned i = blockIdx.x * 256 + threadIdx.x;
+  unsigned work = 0;
+  int state = 2;
+  if (i < s.m) {
+    const ushort4 p = s.pos[i];
+    const int hz = (int)(p.x / s.cell), hy = (int)(p.y / s.cell), hx = (int)(p.z / s.cell);
+    state = 0;
+#pragma unroll
+    for (int o = 0; o < 27; ++o) {
+      const int z2 = min(max(hz + o / 9 - 1, 0), s.gz - 1), y2 = min(max(hy + o / 3 % 3 - 1, 0), s.gy - 1),
+                x2 = min(max(hx + o % 3 - 1, 0), s.gx - 1);
+      const ushort4 q = s.lead[(z2 * s.gy + y2) * s.gx + x2];
+      const float ddz = (float)((int)p.x - (int)q.x), ddy = (float)((int)p.y - (int)q.y),
+                  ddx = (float)((int)p.z - (int)q.z);
+      const float d2 = ddz * ddz + ddy * ddy + ddx * ddx;
+      if (q.w) state = d2 == 0.0f ? 1 : (d2 < s.d2 ? 2 : state);
+    }
+    s.state[i] = state;
+    if (state == 0) {
+      for (int o = 0; o < 9; ++o) {
+        const int z2 = hz + o / 3 - 1, y2 = hy + o % 3 - 1;
+        if (z2 < 0 || z2 >= s.gz || y2 < 0 || y2 >= s.gy) continue;
+        const int row = (z2 * s.gy + y2) * s.gx;
+        work += s.start[row + min(hx + 1, s.gx - 1) + 1] - s.start[row + max(hx - 1, 0)];
+      }
+    }
+  }
+  const unsigned long long open = __ballot(state == 0);
+  if (open) {                                       // uniform per wavefront
+    unsigned long long w = work;
+    for (int off = 32; off > 0; off >>= 1) w += __shfl_xor(w, off);
+    if ((threadIdx.x & 63) == 0) {
+      atomicAdd(&n_open, (unsigned)__popcll(open));
+      atomicAdd(&n_work, w);
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0 && n_open) {
+    atomicAdd(&s.pick->open, n_open);
+    atomicAdd(&s.pick->work, n_work);
+  }
 }
 
-// One round, a wavefront for `per` candidates (16 where k_drop has left few): among the higher-ranked
-// candidates within D, a kept one drops it, else an undecided one makes it wait
+// One round, a wavefront for kSettlePer candidates: among the higher-ranked candidates within D, a kept one drops it, else an undecided one makes it wait
 // for a later round, else it is kept.  States only ever leave 0, so one read too
 // early costs a round and nothing else.  A walk in rank order by one workgroup
 // spent 2.4 ms on 131 000 candidates of 2000 peaks, these rounds alone 0.34 ms,
-// and after k_drop they take 16 us (all of Find Peaks on 512 x 512 x 928: 3.76 -> 0.60 ms).
+// and after k_drop they take 16 us (all of Find Peaks on 512 x 928 x 928: 3.78 -> 0.56 ms).
 __device__ __forceinline__ void settle_one(const Settle& s, unsigned i, unsigned lane) {
   const unsigned long long key = s.key[i];
   const ushort4 p = s.pos[i];
   const int hz = (int)(p.x / s.cell), hy = (int)(p.y / s.cell), hx = (int)(p.z / s.cell);
   bool wait = false;
-  for (int o = 0; o < (s.flat ? 1 : 9); ++o) {
-    unsigned b = 0, e = s.m;
-    if (!s.flat) {
-      const int z2 = hz + o / 3 - 1, y2 = hy + o % 3 - 1;
-      if (z2 < 0 || z2 >= s.gz || y2 < 0 || y2 >= s.gy) continue;
-      const int row = (z2 * s.gy + y2) * s.gx;
-      b = s.start[row + max(hx - 1, 0)];
-      e = s.start[row + min(hx + 1, s.gx - 1) + 1];
-    }
+  for (int o = 0; o < 9; ++o) {
+    const int z2 = hz + o / 3 - 1, y2 = hy + o % 3 - 1;
+    if (z2 < 0 || z2 >= s.gz || y2 < 0 || y2 >= s.gy) continue;
+    const int row = (z2 * s.gy + y2) * s.gx;
+    const unsigned b = s.start[row + max(hx - 1, 0)], e = s.start[row + min(hx + 1, s.gx - 1) + 1];
     for (unsigned j0 = b; j0 < e; j0 += 64 * 4) {   // four loads of a lane in flight
       unsigned long long kj[4];
       ushort4 q[4];
@@ -519,10 +567,10 @@ __device__ __forceinline__ void settle_one(const Settle& s, unsigned i, unsigned
 }
 
 __global__ __launch_bounds__(256) void k_settle(Settle s) {
-  const unsigned i0 = (blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6)) * s.per;
+  const unsigned i0 = (blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6)) * kSettlePer;
   const unsigned lane = threadIdx.x & 63;
-  if (i0 >= s.m || s.pick->pairs > kSettlePairs) return;   // uniform per wavefront
-  const bool open = lane < s.per && i0 + lane < s.m && s.state[i0 + lane] == 0;
+  if (i0 >= s.m || !rounds_pay(*s.pick, s.m)) return;   // uniform per wavefront
+  const bool open = lane < kSettlePer && i0 + lane < s.m && s.state[i0 + lane] == 0;
   for (unsigned long long todo = __ballot(open); todo; todo &= todo - 1)
     settle_one(s, i0 + (unsigned)__ffsll((long long)todo) - 1, lane);
 }
@@ -530,20 +578,43 @@ __global__ __launch_bounds__(256) void k_settle(Settle s) {
 // Undecided candidates counted, kept ones gathered (the counters cleared before);
 // more than kKeptMax kept ones stand for a list that is not settled here.
 __global__ __launch_bounds__(256) void k_gather(Settle s) {
+  __shared__ unsigned n_wait, n_keep, base;
+  if (threadIdx.x == 0) n_wait = n_keep = 0;
+  __syncthreads();
   const unsigned i = blockIdx.x * 256 + threadIdx.x;
-  if (s.pick->pairs > kSettlePairs) {   // uniform
-    if (i == 0) s.pick->kept = kKeptMax + 1;
-    return;
-  }
-  const int st = i < s.m ? s.state[i] : 2;
+  const int st = i < s.m ? s.state[i] : 2, lane = threadIdx.x & 63;
   const unsigned long long wait = __ballot(st == 0), keep = __ballot(st == 1);
+  unsigned at = 0;
+  if (lane == 0 && wait) atomicAdd(&n_wait, (unsigned)__popcll(wait));
+  if (lane == 0 && keep) at = atomicAdd(&n_keep, (unsigned)__popcll(keep));
+  at = (unsigned)__shfl((int)at, 0) + __popcll(keep & ((1ull << lane) - 1ull));
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (n_wait) atomicAdd(&s.pick->undecided, n_wait);
+    if (n_keep) base = atomicAdd(&s.pick->kept, n_keep);
+  }
+  __syncthreads();
+  if (st == 1 && base + at < kKeptMax) s.kept[base + at] = s.key[i];
+}
+
+// The candidates that are not dropped, in any order: all that the sorted walk needs,
+// as a dropped one lies within D of a kept one that ranks higher.
+__global__ __launch_bounds__(256) void k_left(Settle s, unsigned long long* __restrict__ keys,
+                                              unsigned* __restrict__ counter) {
+  __shared__ unsigned n, base;
+  if (threadIdx.x == 0) n = 0;
+  __syncthreads();
+  const unsigned i = blockIdx.x * 256 + threadIdx.x;
   const int lane = threadIdx.x & 63;
-  if (lane == 0 && wait) atomicAdd(&s.pick->undecided, (unsigned)__popcll(wait));
-  if (keep == 0ull) return;
-  unsigned base = 0;
-  if (lane == 0) base = atomicAdd(&s.pick->kept, (unsigned)__popcll(keep));
-  base = (unsigned)__shfl((int)base, 0) + __popcll(keep & ((1ull << lane) - 1ull));
-  if (st == 1 && base < kKeptMax) s.kept[base] = s.key[i];
+  const bool take = i < s.m && s.state[i] != 2;
+  const unsigned long long bal = __ballot(take);
+  unsigned at = 0;
+  if (lane == 0 && bal) at = atomicAdd(&n, (unsigned)__popcll(bal));
+  at = (unsigned)__shfl((int)at, 0) + __popcll(bal & ((1ull << lane) - 1ull));
+  __syncthreads();
+  if (threadIdx.x == 0 && n) base = atomicAdd(counter, n);
+  __syncthreads();
+  if (take) keys[base + at] = s.key[i];
 }
 
 // Rank of each kept key among the kept, and its place in the output.
@@ -576,6 +647,71 @@ __global__ __launch_bounds__(256) void k_rank(const unsigned long long* __restri
     peaks[3 * rank + 2] = p.z;
     vals[rank] = __uint_as_float(~(unsigned)(key >> 32));
   }
+}
+
+// ---------------------------------------------------------------- short list
+// The rule itself on a list of up to kShortList keys in any order, for a few peaks: one
+// workgroup, its keys in registers; the smallest is the next peak, and those within D
+// of it are gone.  n_found = -1: a longer list.  Bound by vector issue of one CU, 3 us
+// a step, one step a peak whatever the map looks like; the settling is 0.1 ms at the
+// least.
+constexpr int kShortThreads = 1024;
+constexpr int kShortEach = 8;
+constexpr unsigned kShortList = kShortThreads * kShortEach;
+constexpr int kShortPeaks = 16;
+constexpr int64_t kShortWant = 5120;   // (a quarter more where sampled)
+
+__global__ __launch_bounds__(kShortThreads) void k_short(const unsigned long long* __restrict__ keys,
+                                                         const unsigned* __restrict__ count, int* __restrict__ n_found,
+                                                         int ny, int nx, float d2, int top_p, int* __restrict__ peaks,
+                                                         float* __restrict__ vals) {
+  constexpr int W = kShortThreads / 64;
+  __shared__ unsigned long long red[2][W];
+  const unsigned m = *count;
+  const int tid = threadIdx.x, wave = tid >> 6;
+  if (m > kShortList) {                              // uniform
+    if (tid == 0) *n_found = -1;
+    return;
+  }
+  unsigned long long key[kShortEach];
+  ushort4 pos[kShortEach];
+#pragma unroll
+  for (int i = 0; i < kShortEach; ++i) {
+    const unsigned j = (unsigned)i * kShortThreads + tid;
+    key[i] = j < m ? keys[j] : ~0ull;
+    pos[i] = key_pos(key[i], ny, nx);
+  }
+  int found = 0;
+  for (; found < top_p; ++found) {
+    unsigned long long best = key[0];
+#pragma unroll
+    for (int i = 1; i < kShortEach; ++i) best = key[i] < best ? key[i] : best;
+    for (int off = 32; off > 0; off >>= 1) {
+      const unsigned long long o = __shfl_xor(best, off);
+      best = o < best ? o : best;
+    }
+    unsigned long long* r = red[found & 1];
+    if ((tid & 63) == 0) r[wave] = best;
+    __syncthreads();
+    best = r[0];
+#pragma unroll
+    for (int i = 1; i < W; ++i) best = r[i] < best ? r[i] : best;
+    if (best == ~0ull) break;                        // uniform
+    const ushort4 p = key_pos(best, ny, nx);
+    if (tid == 0) {
+      peaks[3 * found + 0] = p.x;
+      peaks[3 * found + 1] = p.y;
+      peaks[3 * found + 2] = p.z;
+      vals[found] = __uint_as_float(~(unsigned)(best >> 32));
+    }
+#pragma unroll
+    for (int i = 0; i < kShortEach; ++i) {
+      const float ddz = (float)((int)p.x - (int)pos[i].x), ddy = (float)((int)p.y - (int)pos[i].y),
+                  ddx = (float)((int)p.z - (int)pos[i].z);
+      if (key[i] == best || ddz * ddz + ddy * ddy + ddx * ddx < d2) key[i] = ~0ull;
+    }
+  }
+  if (tid == 0) *n_found = found;
 }
 
 // ---------------------------------------------------------------- greedy walk
@@ -1100,12 +1236,12 @@ int find_peaks(const float* score, int nz, int ny, int nx, const int32_t lo[3],
   st.pos = reinterpret_cast<ushort4*>(tail);
   st.state = reinterpret_cast<int*>(tail + sm * 8);
   st.kept = reinterpret_cast<unsigned long long*>(tail + sm * 12);
-  st.best = st.kept + kKeptMax;
-  st.lead = reinterpret_cast<ushort4*>(st.best + kMaxCells);
-  st.start = reinterpret_cast<unsigned*>(st.lead + kMaxCells);
+  st.lead = reinterpret_cast<ushort4*>(st.kept + kKeptMax);
   const int ncell = gz * gy * gx;
+  st.best = reinterpret_cast<unsigned long long*>(st.lead + kMaxCells);
+  st.start = reinterpret_cast<unsigned*>(st.best + ncell);   // best, start and fill are cleared as one
   st.fill = st.start + ncell + 1;
-  Pick* pick = reinterpret_cast<Pick*>(st.start + 2 * kMaxCells + 64);
+  Pick* pick = reinterpret_cast<Pick*>(st.best + 2 * kMaxCells + 32);
   st.pick = pick;
   st.ny = ny;
   st.nx = nx;
@@ -1115,56 +1251,80 @@ int find_peaks(const float* score, int nz, int ny, int nx, const int32_t lo[3],
   st.gy = gy;
   st.gx = gx;
 
-  // The threshold comes from a sample of at least 4 million voxels (every 16th
+  // The first threshold comes from a sample of at least 4 million voxels (every 16th
   // (slice, row block) pair of a large map): it only sets how many candidates
   // there are, not the answer.  A quarter more are asked of a sample, whose count
   // is off by a few percent: too few candidates cost the whole search once more.
-  const int sample = (int)std::min<int64_t>(16, std::max<int64_t>(1, nvalid >> 22));
+  // 64 candidates a peak hold maps of noise or of small maxima; broad maxima, ramps and
+  // plateaus need a second search, of 65 536 at least, then of four times the last.
+  // The sorted walk takes lists of that length that do not settle; without a try those
+  // of more than twice what was asked for (equal scores: chains of candidates that
+  // wait for each other) and those after a list whose leaders left many open.
+  const bool few = top_p <= kShortPeaks;
+  const int64_t first = few ? kShortWant : std::max<int64_t>(64 * (int64_t)top_p, 4096);
+  const int64_t second = std::max<int64_t>(64 * (int64_t)top_p, 1 << 16);
   Pick got;
-  for (int64_t want = std::max<int64_t>(64 * (int64_t)top_p, kFlatMax);; want *= 4) {
+  int counted = 0;      // the sample in `hist`
+  bool slopes = true;   // the leaders are expected to drop most candidates
+  for (int64_t want = first;; want = want < second ? second : want * 4) {
+    const int sample = want == first ? (int)std::min<int64_t>(16, std::max<int64_t>(1, nvalid >> 22)) : 1;
     fill_zero(pick, sizeof(Pick), s);
     if (want < nvalid) {
       const unsigned want_s = (unsigned)std::max<int64_t>(1, sample > 1 ? want * 5 / 4 / sample : want);
       for (int level = 0; level < 2; ++level) {
-        fill_zero(hist, kHistBins * 4, s);
-        hipLaunchKernelGGL(k_hist, hgrid, dim3(256), 0, s, score, r, level, pick, sample, hist);
-        hipLaunchKernelGGL(k_pick, dim3(1), dim3(1024), 0, s, hist, level, want_s, pick);
+        // the second level's bins lie where the kept keys go later: the first
+        // level's, once they count every voxel, serve all searches
+        unsigned* bins = level ? reinterpret_cast<unsigned*>(st.kept) : hist;
+        if (level || counted != 1) {
+          fill_zero(bins, kHistBins * 4, s);
+          hipLaunchKernelGGL(k_hist, hgrid, dim3(256), 0, s, score, r, level, pick, sample, bins);
+        }
+        hipLaunchKernelGGL(k_pick, dim3(1), dim3(1024), 0, s, bins, level, want_s, pick);
       }
+      counted = sample;
     }
     hipLaunchKernelGGL(k_compact, cgrid, dim3(256), 0, s, score, r, &pick->key_lo, keys_a, &pick->count);
+    if (few && want == first)
+      hipLaunchKernelGGL(k_short, dim3(1), dim3(kShortThreads), 0, s, keys_a, &pick->count, &pick->n_found, ny, nx,
+                         st.d2, top_p, peaks_out, vals_out);
     TTM_HIP(hipGetLastError());   // a launch that failed leaves counts that mean nothing
     TTM_HIP(hipMemcpyAsync(&got, pick, sizeof(Pick), hipMemcpyDeviceToHost, s));
     TTM_HIP(hipStreamSynchronize(s));
-    const int64_t m = got.count;
+    int64_t m = got.count;
     const bool all = m >= nvalid || got.key_lo == 0;
-    if (m <= (int64_t)kSettleMax) {
+    if (few && want == first && got.n_found >= 0) {
+      if (got.n_found >= top_p || all) {
+        *n_found_host = got.n_found;
+        return 0;
+      }
+      slopes = false;
+      continue;
+    }
+    if (slopes && m <= (int64_t)kSettleMax && m <= 2 * want) {
       st.m = (unsigned)m;
       const dim3 mg((unsigned)((m + 255) / 256));
-      st.flat = m <= (int64_t)kFlatMax;
-      st.per = st.flat ? 1 : 16;
-      if (!st.flat) {
-        fill_zero(st.start, (2 * (size_t)ncell + 1) * 4, s);
-        hipLaunchKernelGGL(k_cells<false>, mg, dim3(256), 0, s, st);
-        hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, st.start, ncell + 1);
-        hipLaunchKernelGGL(k_pairs, dim3((ncell + 255) / 256), dim3(256), 0, s, st);
-      }
-      if (m > 0) hipLaunchKernelGGL(k_cells<true>, mg, dim3(256), 0, s, st);
-      if (!st.flat) {
-        hipLaunchKernelGGL(k_lead, dim3((ncell + 3) / 4), dim3(256), 0, s, st);
-        hipLaunchKernelGGL(k_drop, mg, dim3(256), 0, s, st);
-      }
-      for (int look = 0; look == 0 || (got.undecided && got.pairs <= kSettlePairs && look < kSettleLooks); ++look) {
+      fill_zero(st.best, (size_t)ncell * 8 + (2 * (size_t)ncell + 1) * 4, s);
+      hipLaunchKernelGGL(k_cells<false>, mg, dim3(256), 0, s, st);
+      hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, st.start, ncell + 1);
+      hipLaunchKernelGGL(k_cells<true>, mg, dim3(256), 0, s, st);
+      hipLaunchKernelGGL(k_lead, dim3((ncell + 3) / 4), dim3(256), 0, s, st);
+      hipLaunchKernelGGL(k_drop, mg, dim3(256), 0, s, st);
+      unsigned before = 0;
+      for (int look = 0; look < kSettleLooks; ++look) {
         fill_zero(&pick->undecided, 8, s);
-        if (m > 0) {
-          for (int k = 0; k < kSettleRounds; ++k)
-            hipLaunchKernelGGL(k_settle, dim3((unsigned)((m + 4 * st.per - 1) / (4 * st.per))), dim3(256), 0, s, st);
-          hipLaunchKernelGGL(k_gather, mg, dim3(256), 0, s, st);
-          hipLaunchKernelGGL(k_rank, dim3(kKeptMax / 64), dim3(256), 0, s, st.kept, pick, ny, nx, top_p,
-                             peaks_out, vals_out);
-        }
+        for (int k = 0; k < kSettleRounds; ++k)
+          hipLaunchKernelGGL(k_settle, dim3((unsigned)((m + 4 * kSettlePer - 1) / (4 * kSettlePer))), dim3(256), 0, s, st);
+        hipLaunchKernelGGL(k_gather, mg, dim3(256), 0, s, st);
+        hipLaunchKernelGGL(k_rank, dim3(kKeptMax / 64), dim3(256), 0, s, st.kept, pick, ny, nx, top_p,
+                           peaks_out, vals_out);
         TTM_HIP(hipGetLastError());
         TTM_HIP(hipMemcpyAsync(&got, pick, sizeof(Pick), hipMemcpyDeviceToHost, s));
         TTM_HIP(hipStreamSynchronize(s));
+        if (look == 0) before = got.open;
+        slopes = 4ull * got.open <= st.m;
+        // a look that leaves more than half of the last one's: chains, one peak a round
+        if (!got.undecided || 2ull * got.undecided > before || !rounds_pay(got, st.m)) break;
+        before = got.undecided;
       }
       if (!got.undecided && got.kept <= kKeptMax) {
         if (got.n_found >= top_p || all) {
@@ -1172,6 +1332,12 @@ int find_peaks(const float* score, int nz, int ny, int nx, const int32_t lo[3],
           return 0;
         }
         continue;
+      }
+      if (want < second) continue;   // a short list is not worth a sort
+      if (2 * ((int64_t)got.undecided + got.kept) < m) {
+        fill_zero(counter, 4, s);
+        hipLaunchKernelGGL(k_left, mg, dim3(256), 0, s, st, keys_a, counter);
+        m = (int64_t)got.undecided + got.kept;
       }
     }
     const size_t mpad = ((size_t)m + kSortTile - 1) / kSortTile * kSortTile;
@@ -1182,7 +1348,9 @@ int find_peaks(const float* score, int nz, int ny, int nx, const int32_t lo[3],
     }
     unsigned long long* src = keys_a;
     unsigned long long* dst = keys_b;
-    for (int shift = 0; shift < 64; shift += 8) {
+    // the scores' highest byte, where every candidate has the same
+    const bool one_top = sample == 1 && want < nvalid && got.most >> 4 == got.key_lo >> 24;
+    for (int shift = 0; shift < (one_top ? 56 : 64); shift += 8) {
       if (index_byte_constant(shift, r)) continue;
       hipLaunchKernelGGL(k_rs_hist, dim3(nblk), dim3(kSortBlock), 0, s, src, shift, shist, nblk);
       hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, shist, 256 * nblk);
