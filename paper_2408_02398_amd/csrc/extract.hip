@@ -625,7 +625,7 @@ __global__ __launch_bounds__(64 * kPoolWaves) void k_runs(ExtractArgs a, RunArgs
   const int R = r.per_item;
   const Ws w = ws_layout(a.ws, a.plane);
   const unsigned n_items = r.items.n(a);
-  const unsigned groups = min(gridDim.x, pool_groups((size_t)n_items * R));
+  const unsigned groups = min(gridDim.x, pool_groups((size_t)n_items * R, K));
   if (blockIdx.x >= groups) return;
   if (!CONT && (int)threadIdx.x < R) {
     const float* p = a.starts + 3 * (r.s0 + lane);
@@ -646,6 +646,10 @@ __global__ __launch_bounds__(64 * kPoolWaves) void k_runs(ExtractArgs a, RunArgs
   // chunk state (uniform across the wavefront)
   unsigned chunk_base = 0;
   int chunk_runs = 0, next_q = 0;
+  // the first chunk of a workgroup that starts at once is its own, the rest come from
+  // the counter: with all wavefronts at it, the last of 8192 waits 60 us for its turn
+  const unsigned owners = min(groups, kPoolOwners);
+  bool own = blockIdx.x < owners;
   bool exhausted = n_items == 0;
   // lane state
   float c[K];
@@ -687,10 +691,14 @@ __global__ __launch_bounds__(64 * kPoolWaves) void k_runs(ExtractArgs a, RunArgs
       if (next_q == chunk_runs) {
         if (exhausted) break;
         // next chunk of items
-        unsigned long long base = 0;
-        if (lane == 0) base = atomicAdd(r.ctr, (unsigned long long)chunk);
-        base = (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(base >> 32)) << 32 |
-               (unsigned)__builtin_amdgcn_readfirstlane((int)base);
+        unsigned long long base = (unsigned long long)(blockIdx.x * kPoolWaves + wave) * chunk;
+        if (own) {
+          own = false;
+        } else {
+          if (lane == 0) base = (unsigned long long)owners * kPoolWaves * chunk + atomicAdd(r.ctr, (unsigned long long)chunk);
+          base = (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(base >> 32)) << 32 |
+                 (unsigned)__builtin_amdgcn_readfirstlane((int)base);
+        }
         if (base >= n_items) {
           exhausted = true;
           break;
@@ -1231,7 +1239,7 @@ int launch_multistart(const ExtractArgs& a, Items it, unsigned long long* ctr_ba
     const int nsb = (a.n_starts - b * kStartBlock) < kStartBlock ? (a.n_starts - b * kStartBlock)
                                                                  : kStartBlock;
     RunArgs r{it, nsb, b * kStartBlock, ctr_base + b};
-    hipLaunchKernelGGL((k_runs<N, false>), dim3(pool_groups(a.plane * nsb)), dim3(64 * kPoolWaves), 0, s, a, r);
+    hipLaunchKernelGGL((k_runs<N, false>), dim3(pool_groups(a.plane * nsb, ncomp3(N))), dim3(64 * kPoolWaves), 0, s, a, r);
     hipLaunchKernelGGL(k_reduce<N>, dim3(nb), dim3(256), 0, s, a, it, nsb, b == 0 ? 1 : 0,
                        b == n_blocks - 1 ? 1 : 0, merge);
   }
@@ -1262,7 +1270,7 @@ int launch_n(const ExtractArgs& a, hipStream_t s) {
           const unsigned ib = nb < kItemGroups ? nb : kItemGroups;
           hipLaunchKernelGGL((k_prepare<N>), dim3(ib), dim3(256), 0, s, a, cont, 0, 0);
           RunArgs r{cont, 1, 0, ctr + kHdrPoolCont / 2};
-          hipLaunchKernelGGL((k_runs<N, true>), dim3(pool_groups(a.plane)), dim3(64 * kPoolWaves), 0, s, a, r);
+          hipLaunchKernelGGL((k_runs<N, true>), dim3(pool_groups(a.plane, ncomp3(N))), dim3(64 * kPoolWaves), 0, s, a, r);
           hipLaunchKernelGGL(k_learned_post<N>, dim3(ib), dim3(256), 0, s, a);
           compact(w, a.plane, 2, w.fb_list, &w.hdr[kHdrFallbacks], s);
           launch_multistart<N>(a, Items{w.fb_list, &w.hdr[kHdrFallbacks], w.stage}, ctr + kHdrPoolFb / 2,

@@ -410,7 +410,7 @@ __global__ __launch_bounds__(64 * pool_waves4(N)) void k_runs4(ExtractArgs a, It
   float (&cz)[64] = cz_all[wave];
   const Ws4 w = ws4_layout(a.ws, a.plane);
   const unsigned n_items = (unsigned)it.n(a);
-  const unsigned groups = min(gridDim.x, pool_groups((size_t)n_items * R) * (4 / W));
+  const unsigned groups = min(gridDim.x, pool_groups((size_t)n_items * R, K) * (4 / W));
   if (blockIdx.x >= groups) return;
   if ((int)threadIdx.x < R) {
     const float* sv = a.starts + 4 * (s0 + lane);
@@ -428,6 +428,10 @@ __global__ __launch_bounds__(64 * pool_waves4(N)) void k_runs4(ExtractArgs a, It
   const unsigned chunk = per_wave < 1 ? 1 : (per_wave > 64 ? 64 : per_wave);
   unsigned chunk_base = 0;
   int chunk_runs = 0, next_q = 0;
+  // the first chunk of a workgroup that starts at once is its own, the rest come from
+  // the counter: with all wavefronts at it, the last of 8192 waits 60 us for its turn
+  const unsigned owners = min(groups, (N <= 4 ? kPoolOwners : kPoolOwners / 2));
+  bool own = blockIdx.x < owners;
   bool exhausted = n_items == 0;
   float c[K];
 #pragma unroll
@@ -468,10 +472,14 @@ __global__ __launch_bounds__(64 * pool_waves4(N)) void k_runs4(ExtractArgs a, It
     while (n_wait > 0) {
       if (next_q == chunk_runs) {
         if (exhausted) break;
-        unsigned long long base = 0;
-        if (lane == 0) base = atomicAdd(ctr, (unsigned long long)chunk);
-        base = (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(base >> 32)) << 32 |
-               (unsigned)__builtin_amdgcn_readfirstlane((int)base);
+        unsigned long long base = (unsigned long long)(blockIdx.x * W + wave) * chunk;
+        if (own) {
+          own = false;
+        } else {
+          if (lane == 0) base = (unsigned long long)owners * W * chunk + atomicAdd(ctr, (unsigned long long)chunk);
+          base = (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(base >> 32)) << 32 |
+                 (unsigned)__builtin_amdgcn_readfirstlane((int)base);
+        }
         if (base >= n_items) {
           exhausted = true;
           break;
@@ -845,7 +853,7 @@ void launch_multistart4(const ExtractArgs& a, const Items4& it, int merge, hipSt
   for (int b = 0; b < n_blocks; ++b) {
     const int nsb = (a.n_starts - b * kStartBlock4) < kStartBlock4 ? (a.n_starts - b * kStartBlock4)
                                                                    : kStartBlock4;
-    hipLaunchKernelGGL(k_runs4<N>, dim3(pool_groups(a.plane * nsb) * (4 / pool_waves4(N))),
+    hipLaunchKernelGGL(k_runs4<N>, dim3(pool_groups(a.plane * nsb, ncomp4(N)) * (4 / pool_waves4(N))),
                        dim3(64 * pool_waves4(N)), 0, s, a, it, nsb, b * kStartBlock4, w.ctr + b);
     hipLaunchKernelGGL(k_reduce4<N>, dim3(ib), dim3(256), 0, s, a, it, nsb, b == 0 ? 1 : 0,
                        b == n_blocks - 1 ? 1 : 0, merge);

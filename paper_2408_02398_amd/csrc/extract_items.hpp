@@ -56,17 +56,28 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// Pooled workgroups for so many runs.  A run of max_iter updates is a serial chain,
-// and it advances at its wavefront's share of the SIMD: few runs end soonest with one
-// wavefront per SIMD (a workgroup per CU), many with all that fit.  Score and
-// orientation of e^3 voxels of degree 4 with 256 / 512 / 768 / 1024 / 2048 workgroups:
-// e = 24 (220 000 runs) 226 / 270 / 286 / 390 / 419 us, e = 32 (520 000) 322 / 291 /
-// 335 / 419 / 646, e = 40 (1.0 million) - / - / 355 / 418 / -, e = 48 (1.8 million)
-// 725 / 475 / 422 / 447 / 593, e = 64 (4.2 million) 1431 / 866 / 725 /
-// 673 / 690, e = 80 (8.2 million) 2625 / 1578 / - / 1170 / 1110; degree 6 changes at
-// the same counts.
-__host__ __device__ inline unsigned pool_groups(size_t runs) {
-  return runs < 350000 ? 256 : runs < 750000 ? 512 : runs < 2000000 ? 768 : runs < 4000000 ? 1024 : 2048;
+// Pooled workgroups that are on the chip from the start, whatever their LDS and registers (half
+// as many of the quaternion form's at degree 6).
+constexpr unsigned kPoolOwners = 1024;
+
+// Pooled workgroups for so many runs of a tensor of K components.  A run of max_iter
+// updates is a serial chain, and it advances at its wavefront's share of the SIMD: few
+// runs end soonest with one wavefront per SIMD (a workgroup per CU), many with all that
+// fit.  A workgroup also costs 0.1 us, in chunks taken from one counter, which short
+// runs (tensors near one direction) do not hide.  Score and orientation of e^3 voxels with
+// 256 / 512 / 768 / 1024 / 2048 workgroups, 16 starts:
+//   degree 4, field of a tomogram: e = 32 (0.5 million runs) 307 / 267 / 301 / 364 / 609 us,
+//     48 (1.8) 708 / 446 / 386 / 396 / 551, 64 (4.2) 1409 / 833 / 699 / 624 / 656,
+//     80 (8.2) 2590 / 1539 / 1256 / 1139 / 1062, 97 (15) 4440 / 2537 / 2113 / 2003 / 1889
+//   degree 4, one direction and 1 % noise: e = 24 (0.2) 91 / 132 / 131 / 215 / 262,
+//     64 286 / 236 / 250 / 292 / 532, 96 (14) 878 / 583 / 489 / 482 / 680
+//   degree 6: 64 2094 / 1288 / 1105 / 1041 / 1018 and 512 / 393 / 361 / 381 / 598,
+//     97 6407 / 3875 / 3392 / 3236 / 3308 and (96) 1536 / 1045 / 910 / 884 / 933
+//   quaternions, degree 4, 1 %: 32 174 / 218 / 247 / 316 / 530, 64 514 / 412 / 381 / 423 / 659,
+//     96 (14) 1607 / 1183 / 1059 / 1035 / 1131
+// 2048 thus wait for work of 350 million components (14 million runs at degree 6).
+__host__ __device__ inline unsigned pool_groups(size_t runs, int K) {
+  return runs < 350000 ? 256 : runs < 750000 ? 512 : runs < 2000000 ? 768 : runs * K < 350000000 ? 1024 : 2048;
 }
 
 }  // namespace ttm
