@@ -75,16 +75,37 @@ __global__ __launch_bounds__(kRowsX / 2 * Plan<N>::T) void k_r2c_x(RealSrc src, 
     constexpr int NTH = NP * T, IT = kRowsX * N / NTH;
     static_assert(kRowsX * N % NTH == 0, "tile rows");
     const double center = src.center ? src.center[0] : 0.0;
-    float ld[IT];  // all loads in flight, then the LDS stores
+    if constexpr (IT <= 32) {
+      float ld[IT];  // all loads in flight, then the LDS stores
 #pragma unroll
-    for (int i = 0; i < IT; ++i) {
-      const int e = tid + i * NTH;
-      ld[i] = load_src(src, b, z, y0 + e / N, e % N);
-    }
+      for (int i = 0; i < IT; ++i) {
+        const int e = tid + i * NTH;
+        ld[i] = load_src(src, b, z, y0 + e / N, e % N);
+      }
 #pragma unroll
-    for (int i = 0; i < IT; ++i) {
-      const int e = tid + i * NTH;
-      rows[(e / N) * RS + e % N] = src_value(src, b, z, y0 + e / N, e % N, ld[i], center);
+      for (int i = 0; i < IT; ++i) {
+        const int e = tid + i * NTH;
+        rows[(e / N) * RS + e % N] = src_value(src, b, z, y0 + e / N, e % N, ld[i], center);
+      }
+    } else {
+      // edge 160: 40 loads at once with their index arithmetic take every register
+      // and leave one wavefront on a SIMD (41 us a tile and its square; 28 in parts)
+      constexpr int PL = IT / 4;
+      static_assert(IT % PL == 0, "whole parts");
+#pragma unroll 1
+      for (int e0 = tid; e0 < kRowsX * N; e0 += PL * NTH) {
+        float ld[PL];
+#pragma unroll
+        for (int i = 0; i < PL; ++i) {
+          const int e = e0 + i * NTH;
+          ld[i] = load_src(src, b, z, y0 + e / N, e % N);
+        }
+#pragma unroll
+        for (int i = 0; i < PL; ++i) {
+          const int e = e0 + i * NTH;
+          rows[(e / N) * RS + e % N] = src_value(src, b, z, y0 + e / N, e % N, ld[i], center);
+        }
+      }
     }
   }
   __syncthreads();
