@@ -685,15 +685,17 @@ int inverse_n(const cf* G, const cf* Sp, size_t s_stride, int s_planes, int A, c
     while (jp < E && jp * T < s_planes) jp *= 2;
   }
   // Few columns (a 96^3 tile has 294 workgroups of two wavefronts) leave the
-  // chip idle while every workgroup walks all A components, so the components
-  // are split until 4096 workgroups are in the grid; at least 4 components stay
-  // together (2 where the columns alone do not give each CU a workgroup),
+  // chip idle while every workgroup walks all A components, so up to 160 the
+  // components are split until 4096 workgroups are in the grid; at least 4 components
+  // stay together (2 where the columns alone do not give each CU a workgroup),
   // because each part reads G again.  K = 28: 96^3 75 -> 45 us, 128^3 75 -> 62 us,
-  // 256^3 571 -> 549 us, 64^3 (K = 15) 19 -> 8.5 us; 512^3 is not split.
+  // 64^3 (K = 15) 19 -> 8.5 us.  From 192 on the read of G counts for more, and the Y
+  // pass finds less of its input in the caches: 256^3 in two parts, both passes
+  // together, K = 6 227 -> 243 us, K = 28 1223 -> 1228.
   auto launch = [&](auto kern, int cb) {
     const int nblk = NROWS / cb, least = nblk < 256 ? 2 : 4;
-    const int parts = std::max(1, std::min((A + least - 1) / least, 4096 / nblk + (4096 % nblk != 0)));
-    const int ac = nblk < 4096 ? (A + parts - 1) / parts : A;
+    const int parts = N < 192 ? std::max(1, std::min((A + least - 1) / least, 4096 / nblk + (4096 % nblk != 0))) : 1;
+    const int ac = (A + parts - 1) / parts;
     hipLaunchKernelGGL(kern, dim3(nblk, gb, (A + ac - 1) / ac), dim3(cb * T), 0, s, G, Sp, s_stride,
                        s_planes, A, center, work, work_stride, zlim, tw, g_stride, ac);
   };
