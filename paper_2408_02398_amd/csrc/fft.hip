@@ -19,7 +19,7 @@ namespace ttm {
 namespace {
 
 constexpr int kRowsX = 16;  // real rows per workgroup in the X passes (packed in pairs)
-constexpr int kRowsC = 16;  // output rows of an inverse X workgroup (32: 12 wavefronts on a CU instead of 18; 35 components of 197^3 at 256 643 us against 578)
+constexpr int kRowsV = 16;  // rows of an inverse X workgroup that forms w: 8 of each local sum
 
 // Tile element (z, y, x) of batch b, read at the nearest source voxel: the
 // address is always in bounds, so a thread's loads need no branch and are in
@@ -483,18 +483,19 @@ __global__ __launch_bounds__(PlaneWg<N>::NTH) __attribute__((amdgpu_waves_per_eu
 }
 
 // ---------------------------------------------------------------- X inverse
-// VAR: the two local sums' spectra (spec_stride apart), kRowsC / 2 rows of each, and
+// RC output rows of a component in a workgroup (see inverse_n).
+// VAR: the two local sums' spectra (spec_stride apart), RC / 2 rows of each, and
 // w formed from them in place of two stores, two loads and a launch (512^3 tile:
 // 901 -> 529 us for the sums and w, 256^3: 107 -> 77).  Rows are packed in pairs of one sum:
 // packed across the sums, each would carry rounding on the other's scale.
-template <int N, bool VAR>
-__global__ __launch_bounds__(kRowsC / 2 * Plan<N>::T) __attribute__((amdgpu_waves_per_eu(N == 512 ? 8 : 1))) void k_c2r_x(const cf* __restrict__ spec,
+template <int N, int RC, bool VAR>
+__global__ __launch_bounds__(RC / 2 * Plan<N>::T) __attribute__((amdgpu_waves_per_eu(N == 512 ? 8 : 1))) void k_c2r_x(const cf* __restrict__ spec,
                                                           size_t spec_stride, int A, RealDst dst,
                                                           VarDst var, const cf* __restrict__ tw) {
-  constexpr int T = Plan<N>::T, E = N / T, NP = kRowsC / 2, NH = N / 2 + 1;
+  constexpr int T = Plan<N>::T, E = N / T, NP = RC / 2, NH = N / 2 + 1;
   constexpr int S = lds_stride<N>();
   constexpr int SPS = NH + 1;  // padded spectrum row
-  constexpr int BYTES_A = kRowsC * SPS * 8, BYTES_B = NP * S * 8, BYTES_C = kRowsC * (N + 4) * 4;
+  constexpr int BYTES_A = RC * SPS * 8, BYTES_B = NP * S * 8, BYTES_C = RC * (N + 4) * 4;
   constexpr int BYTES = BYTES_A > BYTES_B ? (BYTES_A > BYTES_C ? BYTES_A : BYTES_C)
                                           : (BYTES_B > BYTES_C ? BYTES_B : BYTES_C);
   __shared__ __align__(16) unsigned char smem[BYTES];
@@ -504,14 +505,14 @@ __global__ __launch_bounds__(kRowsC / 2 * Plan<N>::T) __attribute__((amdgpu_wave
   const int tid = threadIdx.x;
   // work items: component fastest, then row block, then z plane, so the
   // workgroups that share a crop's weight-map rows run together in one XCD
-  constexpr int RW = VAR ? kRowsC / 2 : kRowsC;   // output rows
+  constexpr int RW = VAR ? RC / 2 : RC;   // output rows
   constexpr int NYB = N / RW;
   const int item = (int)xcd_item(blockIdx.x, gridDim.x);
   if constexpr (VAR) A = 1;
   const int b = item % A, y0 = (item / A) % NYB * RW, z = item / A / NYB;
   if (z >= dst.sz || y0 >= dst.sy) return;  // uniform: nothing of this block is kept
   const int p = tid / T, t = tid % T;
-  constexpr int NTH = NP * T, NIN = NH * kRowsC, IT = (NIN + NTH - 1) / NTH;
+  constexpr int NTH = NP * T, NIN = NH * RC, IT = (NIN + NTH - 1) / NTH;
   const cf* in = spec + b * spec_stride + (size_t)z * NH * N + y0;
   {
     // all loads first (indices clamped, so every one is in bounds), then the
@@ -523,13 +524,13 @@ __global__ __launch_bounds__(kRowsC / 2 * Plan<N>::T) __attribute__((amdgpu_wave
 #pragma unroll
     for (int i = 0; i < IT; ++i) {
       const int e = min(tid + i * NTH, NIN - 1);
-      const unsigned half = VAR && e % kRowsC >= RW ? (unsigned)spec_stride : 0u;
-      ld[i] = e % RW < nrows_in ? at_byte(in, (half + (unsigned)((e / kRowsC) * N + e % RW)) * 8u) : cf{0.0f, 0.0f};
+      const unsigned half = VAR && e % RC >= RW ? (unsigned)spec_stride : 0u;
+      ld[i] = e % RW < nrows_in ? at_byte(in, (half + (unsigned)((e / RC) * N + e % RW)) * 8u) : cf{0.0f, 0.0f};
     }
 #pragma unroll
     for (int i = 0; i < IT; ++i) {
       const int e = tid + i * NTH;
-      if (e < NIN) sp[(e % kRowsC) * SPS + e / kRowsC] = ld[i];
+      if (e < NIN) sp[(e % RC) * SPS + e / RC] = ld[i];
     }
   }
   FftTw<N> twr;  // in flight across the barrier
@@ -585,7 +586,7 @@ __global__ __launch_bounds__(kRowsC / 2 * Plan<N>::T) __attribute__((amdgpu_wave
   // one output column x of one group of RH rows per thread and pass: the
   // group's weight-map loads (row indices clamped into the crop) are in flight
   // together
-  constexpr int RH = 16, NG = kRowsC / RH;
+  constexpr int RH = 16, NG = RC / RH;
   for (int i = tid; i < sx * NG; i += NTH) {
     const int g = i / sx, x = i - g * sx, r0 = g * RH;
     float val[RH];
@@ -717,12 +718,23 @@ int inverse_n(const cf* G, const cf* Sp, size_t s_stride, int s_planes, int A, c
     hipLaunchKernelGGL((k_c2c_rows<N, true>), dim3(NROWS / RB, nb), dim3(RB * T), 0, s, work,
                        work_stride, zlim, dst.sy, tw);
     static_assert(inverse_fuses_variance(N), "the sums' rows in the X pass");
+    auto rows = [&](auto kern, int rc, int items, const VarDst& v) {
+      hipLaunchKernelGGL(kern, dim3(items * N), dim3(rc / 2 * T), 0, s, work, work_stride, nb, dst, v, tw);
+    };
+    // Rows of a workgroup: 16 put more wavefronts on a CU, 32 read the columns in pieces of
+    // 256 bytes.  512: 16 (28 components of 473^3 6.63 -> 6.54 ms, bfloat16 5.89 -> 5.57).
+    // Below, 32 are 4 to 7 % faster (28 components of 249^3 at 256 866 us against 925,
+    // 160^3 at 192 287 against 301; bfloat16 4 %), unless 16 spare half a block of at most
+    // 7 (8 for bfloat16): 197^3 at 256 634 us either way, bfloat16 568 -> 548, 35
+    // components 614 -> 571.
+    const int blocks = (dst.sy + 31) / 32;
+    const bool half = (dst.sy - 1) % 32 < 16 && blocks <= (dst.dtype == 1 ? 8 : 7);
     if (var) {
-      hipLaunchKernelGGL((k_c2r_x<N, true>), dim3(N / (kRowsC / 2) * N), dim3(kRowsC / 2 * T), 0, s, work,
-                         work_stride, nb, dst, *var, tw);
-    } else {
-      hipLaunchKernelGGL((k_c2r_x<N, false>), dim3(nb * (N / kRowsC) * N), dim3(kRowsC / 2 * T), 0, s, work,
-                         work_stride, nb, dst, VarDst{}, tw);
+      rows(k_c2r_x<N, kRowsV, true>, kRowsV, N / (kRowsV / 2), *var);
+    } else if (N == 512 || half) {
+      rows(k_c2r_x<N, 16, false>, 16, nb * (N / 16), VarDst{});
+    } else if constexpr (N != 512) {
+      rows(k_c2r_x<N, 32, false>, 32, nb * (N / 32), VarDst{});
     }
   }
   hipError_t e = hipGetLastError();
