@@ -1050,7 +1050,7 @@ __global__ __launch_bounds__(64 * kLearnedWaves) __attribute__((amdgpu_waves_per
     put_features<2>(xs, lane, [&](int k) { return k < K ? bf16_bits(sqrtf(sy.mu[k]) * c[k] * inv) : (unsigned short)0; });
     wave_lds_sync();
     float y0, y1, y2;
-    mlp_forward_w(xs, net, lane, y0, y1, y2);
+    mlp_forward_w<2>(xs, net, lane, y0, y1, y2);
     const float ny = sqrtf(y0 * y0 + y1 * y1 + y2 * y2);
     const bool forced = !(ny > 0.0f);
     float ux = forced ? s0x : y0, uy = forced ? s0y : y1, uz = forced ? s0z : y2;

@@ -763,7 +763,7 @@ __global__ __launch_bounds__(64 * kLearnedWaves4) void k_learned4(ExtractArgs a)
     put_features<KT>(xs, lane, [&](int k) { return k < K ? bf16_bits(sqrtf(sy.mu[k]) * c[k] * inv) : (unsigned short)0; });
     wave_lds_sync();
     float y[4];
-    mlp_forward_t<KT>(xs, net, lane, y);
+    mlp_forward_t<KT, 4>(xs, net, lane, y);
     wave_lds_sync();   // xs is rewritten by the next group
     const float ny = sqrtf(y[0] * y[0] + y[1] * y[1] + y[2] * y[2] + y[3] * y[3]);
     const bool forced = !(ny > 0.0f);

@@ -216,33 +216,36 @@ __device__ __forceinline__ void put_features(unsigned short* xs, int lane, F f) 
 // for a network of KT input tiles.
 //   xs: this wavefront's features in LDS (put_features), 8-byte aligned and made
 //       visible to the wavefront before the call.
+// NT tiles of 16 voxels at a time: all four read the weights once, two hold half the
+// registers.  Two where that makes room for another wavefront (k_learned, three to
+// four on a SIMD); elsewhere it does not, and four are faster: quaternions of degree 2,
+// 97^3 voxels 104 us against 114, k_mlp_start 38 against 40.
 // Returns y[0..3] (the first four outputs) of the calling lane's voxel.
-template <int KT, class W>
+template <int KT, int NT, class W>
 __device__ __forceinline__ void mlp_forward_t(const unsigned short* xs, const W& w, int lane,
                                               float (&y)[4]) {
   const int r16 = lane & 15, q = lane >> 4;
 #pragma unroll
   for (int i = 0; i < 4; ++i) y[i] = 0.0f;
-  // two tiles of 16 voxels at a time: all four would hold twice the registers
 #pragma unroll 1
-  for (int n0 = 0; n0 < 4; n0 += 2) {
-    asm volatile("" ::: "memory");   // the weights stay in LDS between the passes
+  for (int n0 = 0; n0 < 4; n0 += NT) {
+    if constexpr (NT < 4) asm volatile("" ::: "memory");   // the weights stay in LDS between the passes
     // B fragments of X^T: lane L holds x[voxel 16 nt + L % 16][feature 16 s + 4 (L/16) + j]
-    bf16x4 xb[KT][2];
+    bf16x4 xb[KT][NT];
 #pragma unroll
     for (int s = 0; s < KT; ++s)
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
+      for (int nt = 0; nt < NT; ++nt)
         xb[s][nt] = *reinterpret_cast<const bf16x4*>(xs + 4 * xs_group<KT>(16 * (n0 + nt) + r16, 4 * s + q));
-    // layer 1: H1^T (64 x 32) = W1^T (64 x 16 KT) X^T (16 KT x 32)
-    bf16x4 h1[4][2];
+    // layer 1: H1^T (64 x 16 NT) = W1^T (64 x 16 KT) X^T (16 KT x 16 NT)
+    bf16x4 h1[4][NT];
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
       bf16x4 a[KT];
 #pragma unroll
       for (int s = 0; s < KT; ++s) a[s] = w.w1(4 * s + m);
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
+      for (int nt = 0; nt < NT; ++nt) {
         f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s = 0; s < KT; ++s) acc = mfma16(a[s], xb[s][nt], acc);
@@ -250,25 +253,25 @@ __device__ __forceinline__ void mlp_forward_t(const unsigned short* xs, const W&
       }
     }
     // layer 2: H2^T = W2^T H1^T
-    bf16x4 h2[4][2];
+    bf16x4 h2[4][NT];
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
       bf16x4 a[4];
 #pragma unroll
       for (int s = 0; s < 4; ++s) a[s] = w.w2(s * 4 + m);
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
+      for (int nt = 0; nt < NT; ++nt) {
         f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s = 0; s < 4; ++s) acc = mfma16(a[s], h1[s][nt], acc);
         h2[m][nt] = relu_bf16_w(acc, w, 2, m);
       }
     }
-    // layer 3: Y^T (16 x 32) = W3^T H2^T; lanes 0..15 hold rows 0..3 (outputs)
+    // layer 3: Y^T (16 x 16 NT) = W3^T H2^T; lanes 0..15 hold rows 0..3 (outputs)
     // of voxel columns 16 nt + lane, and each voxel lane fetches its outputs from
     // lane (voxel % 16) of tile voxel / 16
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
+    for (int nt = 0; nt < NT; ++nt) {
       f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int s = 0; s < 4; ++s) acc = mfma16(w.w3(s), h2[s][nt], acc);
@@ -282,11 +285,11 @@ __device__ __forceinline__ void mlp_forward_t(const unsigned short* xs, const W&
 }
 
 // The K <= 32 network with three outputs (d' = 3).
-template <class W>
+template <int NT, class W>
 __device__ __forceinline__ void mlp_forward_w(const unsigned short* xs, const W& w, int lane,
                                               float& y0, float& y1, float& y2) {
   float y[4];
-  mlp_forward_t<2>(xs, w, lane, y);
+  mlp_forward_t<2, NT>(xs, w, lane, y);
   y0 = y[0];
   y1 = y[1];
   y2 = y[2];
@@ -297,7 +300,7 @@ __device__ __forceinline__ void mlp_forward_w(const unsigned short* xs, const W&
 __device__ __forceinline__ void mlp_forward(const unsigned short* xs, const MlpRegs& w, int lane,
                                             float& y0, float& y1, float& y2) {
   __syncthreads();
-  mlp_forward_w(xs, MlpRegView{w}, lane, y0, y1, y2);
+  mlp_forward_w<4>(xs, MlpRegView{w}, lane, y0, y1, y2);
 }
 
 }  // namespace ttm
