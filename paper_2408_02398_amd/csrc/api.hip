@@ -924,6 +924,11 @@ size_t spec_elems(int N) { return (size_t)N * (N / 2 + 1) * N; }
 // x/y-transformed template: its L nonzero z planes only
 size_t tspec_elems(int N, int L) { return (size_t)L * (N / 2 + 1) * N; }
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
+// One local sum of a tile, where it is stored (0: w is formed in the inverse pass).
+size_t local_sum_bytes(int N, int L) {
+  const size_t step = (size_t)(N - L + 1);
+  return inverse_fuses_variance(N) ? 0 : align256(step * step * step * 4);
+}
 
 size_t wedge_workspace(int L, int K) {
   const int P = wedge_box(L), B = wedge_batch(P);
@@ -1032,8 +1037,7 @@ size_t ttm_workspace_size(const ttm_desc* desc, int op, int fft_n, int nz, int n
       return align256(prefilter_blocks(nz, ny, nx) * 16);
     case TTM_OP_NORMALIZE: {
       if (!fft_ok(fft_n) || desc->L > fft_n) return 0;
-      const size_t step = (size_t)(fft_n - desc->L + 1);
-      return 4 * align256(spec_elems(fft_n) * 8) + 2 * align256(step * step * step * 4) +
+      return 4 * align256(spec_elems(fft_n) * 8) + 2 * local_sum_bytes(fft_n, desc->L) +
              align256(prefilter_blocks(nz, ny, nx) * 16);
     }
     case TTM_OP_CORRELATE:
@@ -1056,9 +1060,7 @@ size_t ttm_workspace_size(const ttm_desc* desc, int op, int fft_n, int nz, int n
       return wedge_workspace(desc->L, K);
     case TTM_OP_NORM_CORR: {
       if (!fft_ok(fft_n) || desc->L > fft_n) return 0;
-      const size_t step = (size_t)(fft_n - desc->L + 1);
-      return (size_t)(2 + std::max(K, 2)) * align256(spec_elems(fft_n) * 8) +
-             2 * align256(step * step * step * 4);
+      return (size_t)(2 + std::max(K, 2)) * align256(spec_elems(fft_n) * 8) + 2 * local_sum_bytes(fft_n, desc->L);
     }
     default:
       return 0;
@@ -1232,12 +1234,13 @@ int normalize_boxes(ttm_ctx* ctx, const ttm_desc* desc, const float* g, int nz, 
   const size_t sb = align256(se * 8);
   const int step = fft_n - L + 1;
   // G of the centred tile and of its square (sb bytes apart), their two
-  // products' work spectra, the local sums s1 and s2 (s_gap floats apart)
+  // products' work spectra, the local sums s1 and s2 where they are stored
+  // (s_gap floats apart)
   char* w = static_cast<char*>(ws);
   cf* G1 = reinterpret_cast<cf*>(w);
   cf* work = reinterpret_cast<cf*>(w + 2 * sb);
-  const size_t s_gap = align256((size_t)step * step * step * 4) / 4;
-  float* s1 = reinterpret_cast<float*>(w + 4 * sb);
+  const size_t s_gap = local_sum_bytes(fft_n, L) / 4;
+  float* s1 = s_gap ? reinterpret_cast<float*>(w + 4 * sb) : nullptr;
   float* s2 = s1 + s_gap;
   const int c = L / 2;
   const double M = mask_count(L, desc->mask_radius);
@@ -1363,9 +1366,7 @@ int ttm_normalize(ttm_ctx* ctx, const ttm_desc* desc, const float* vol, int nz, 
   hipStream_t s = static_cast<hipStream_t>(stream);
   TTM_HIP(hipSetDevice(ctx->device));
   const size_t sb = align256(spec_elems(fft_n) * 8);
-  const size_t step = (size_t)(fft_n - L + 1);
-  double* part = reinterpret_cast<double*>(static_cast<char*>(ws) + 4 * sb +
-                                           2 * align256(step * step * step * 4));
+  double* part = reinterpret_cast<double*>(static_cast<char*>(ws) + 4 * sb + 2 * local_sum_bytes(fft_n, L));
   prefilter_stats(desc, vol, nz, ny, nx, g_out, stats_out, part, s);
   fill_zero(w_out, (size_t)nz * ny * nx * 4, s);
   const int c = L / 2;
@@ -1471,12 +1472,12 @@ int ttm_normalize_correlate(ttm_ctx* ctx, const ttm_desc* desc, const float* g, 
   const size_t se = spec_elems(fft_n);
   const size_t sb = align256(se * 8);
   // G of the centred tile and of its square (sb bytes apart), max(K, 2) work
-  // spectra, the local sums s1 and s2 (s_gap floats apart)
+  // spectra, the local sums s1 and s2 where they are stored (s_gap floats apart)
   char* w = static_cast<char*>(ws);
   cf* G1 = reinterpret_cast<cf*>(w);
   cf* work = reinterpret_cast<cf*>(w + 2 * sb);
-  const size_t s_gap = align256((size_t)step * step * step * 4) / 4;
-  float* s1 = reinterpret_cast<float*>(w + (2 + std::max(K, 2)) * sb);
+  const size_t s_gap = local_sum_bytes(fft_n, L) / 4;
+  float* s1 = s_gap ? reinterpret_cast<float*>(w + (2 + std::max(K, 2)) * sb) : nullptr;
   float* s2 = s1 + s_gap;
   const double M = mask_count(L, desc->mask_radius);
   const size_t tse = tspec_elems(fft_n, L);

@@ -24,3 +24,16 @@ def test_training_workspace_serves_smaller_batches(degree, dprime):
              (1, 64, 65, 4096, 8191, 8192, 8193, 12000, 12288, 16384, 16385, 24577, 100000, 1 << 20)]
     assert sizes == sorted(sizes)
     assert sizes[0] > 0
+
+
+@pytest.mark.parametrize("N,L", [(160, 24), (192, 24), (256, 40), (512, 40)])
+def test_normalisation_workspace_holds_what_is_stored(N, L):
+    """Spectra, the prefilter's partial sums, and the two local sums up to edge 160 only:
+    from 192 on the inverse pass forms w from them and stores neither."""
+    from paper_2408_02398_amd import _lib as lib
+    from paper_2408_02398_amd import ttm
+    d = ttm.make_desc(6, L, 0.4 * L)
+    spec = (N * (N // 2 + 1) * N * 8 + 255) // 256 * 256
+    sums = 2 * (((N - L + 1) ** 3 * 4 + 255) // 256 * 256) if N <= 160 else 0
+    assert _size(d, lib.TTM_OP_NORM_CORR, N, 0, 0, 0) == (2 + 28) * spec + sums
+    assert _size(d, lib.TTM_OP_NORMALIZE, N, N, N, N) == 4 * spec + sums + _size(d, lib.TTM_OP_PREFILTER, 0, N, N, N)
