@@ -224,7 +224,7 @@ def _greedy(score, lo, hi, top, dist):
     ("ramp", (16, 20, 400), 60, 7.0),        # one chain: each candidate waits for its neighbour
     ("flat", (33, 40, 64), 50, 5.0),         # peaks on an exact zero background, fewer than asked for above it
     ("dense", (24, 25, 24), 2048, 0.0),      # distance 0: every voxel is a peak (the most grid cells)
-    ("blobs", (150, 200, 230), 300, 9.0),    # the threshold's two levels over a sampled map
+    ("blobs", (150, 200, 230), 300, 9.0),    # the threshold's two levels (every voxel counted: a sample is taken from 2^23 on)
 ])
 def test_find_peaks_candidates(T, ctx, kind, shape, top, dist):
     """find_peaks against the rule's definition, bit for bit."""
