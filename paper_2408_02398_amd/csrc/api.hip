@@ -172,11 +172,12 @@ __global__ void k_mask(float* __restrict__ m, int L, float r) {
 // two kernels: S(t) over the whole chip, every thread's 27 loads in flight
 // together, then one workgroup for its sums and the scaling (the box has at most
 // 64^3 voxels).  In one workgroup with each neighbour behind its bounds branch,
-// 40^3 took 200 us; now 69 us.
+// 40^3 took 200 us; now 69 us.  The first one also clears the K components of T.
 __global__ __launch_bounds__(256) void k_template_filter(const float* __restrict__ t, int L, float r, float a,
-                                                         float* __restrict__ tn) {
+                                                         float* __restrict__ tn, int K, float* __restrict__ T) {
   const int i = blockIdx.x * 256 + threadIdx.x, c = L / 2;
   if (i >= L * L * L) return;
+  for (int k = 0; k < K; ++k) T[(size_t)k * L * L * L + i] = 0.0f;
   const float w0 = a, w1 = 1.0f - 2.0f * a;
   const int x = i % L, y = (i / L) % L, z = i / (L * L);
   const int dx = x - c, dy = y - c, dz = z - c;
@@ -249,10 +250,10 @@ __global__ __launch_bounds__(1024) void k_template_norm(int L, float r, float* _
   }
 }
 
-void template_norm(const ttm_desc* d, const float* tmpl, float* tn, hipStream_t s) {
+void template_norm(const ttm_desc* d, const float* tmpl, float* tn, int K, float* T, hipStream_t s) {
   const int L = d->L;
   hipLaunchKernelGGL(k_template_filter, dim3((L * L * L + 255) / 256), dim3(256), 0, s, tmpl, L, d->mask_radius,
-                     d->filter_a, tn);
+                     d->filter_a, tn, K, T);
   hipLaunchKernelGGL(k_template_norm, dim3(1), dim3(1024), 0, s, L, d->mask_radius, tn);
 }
 
@@ -1077,7 +1078,7 @@ int ttm_build_tensor(ttm_ctx* ctx, const ttm_desc* desc, const float* tmpl, cons
   hipStream_t s = static_cast<hipStream_t>(stream);
   TTM_HIP(hipSetDevice(ctx->device));
   const int L = desc->L, K = ncomp(desc->degree, desc->dprime);
-  template_norm(desc, tmpl, tn_out, s);
+  template_norm(desc, tmpl, tn_out, K, T_out, s);
   Exponents ex;
   exponents(desc->degree, desc->dprime, ex);
   float ax = desc->axis[0], ay = desc->axis[1], az = desc->axis[2];
@@ -1089,14 +1090,15 @@ int ttm_build_tensor(ttm_ctx* ctx, const ttm_desc* desc, const float* tmpl, cons
     }
     ax /= an; ay /= an; az /= an;
   }
-  fill_zero(T_out, (size_t)K * L * L * L * 4, s);
   const int lim2 = reach_sq(desc->mask_radius);
   int reach = 0, x0;
   for (int i = 0; i < L * L; ++i) reach += row_reach(lim2, L, i / L, i % L, x0);
   const int R = (int)std::floor(desc->mask_radius);
   int floats = 0;
   for (int z = -R - 1; z <= R + 1; ++z) floats += slice_floats(slice_half(desc->mask_radius, z));
-  if (floats <= kBuildBall && 2 * R + 3 <= kBuildSlices) {
+  // A few rotations do not pay for filling the LDS (1 rotation of 16^3: 38 us, 30 from
+  // global memory; 40^3 128 / 129 us; 32 rotations of 40^3 129 / 132).
+  if (nq > 16 && floats <= kBuildBall && 2 * R + 3 <= kBuildSlices) {
     const int vg = kLdsGroups * kBuildVox;
     for (int a0 = 0; a0 < K; a0 += kCompBlock)
       hipLaunchKernelGGL(k_build_lds, dim3((reach + vg - 1) / vg), dim3(64 * kLdsWaves), 0, s, tn_out, L,
@@ -1146,7 +1148,7 @@ int ttm_build_tensor_wedge(ttm_ctx* ctx, const ttm_desc* desc, const float* tmpl
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
   TTM_HIP(hipSetDevice(ctx->device));
-  template_norm(desc, tmpl, tn_out, s);
+  template_norm(desc, tmpl, tn_out, 0, nullptr, s);
   const int P = wedge_box(L), B = wedge_batch(P);
   const size_t nbox = (size_t)P * P * P, nspec = spec_elems(P), n = (size_t)L * L * L;
   char* p = static_cast<char*>(ws);
