@@ -304,8 +304,8 @@ __host__ __device__ inline int row_reach(int lim2, int L, int z, int y, int& x0)
 // A workgroup takes 32 voxels and all rotations, kBuildWaves chunks at a time
 // (one per wavefront), and adds its wavefronts' totals through LDS: no scratch
 // memory, and a fixed order of summation.  Bound by the gathers of t' (4 row
-// pairs per sample).  40^3, r = 17, 24 000 rotations, K = 28: 6.7 ms, against
-// 38.5 ms with one voxel per lane over the whole box, FP64 accumulators
+// pairs per sample).  64^3, r = 31, 5000 rotations, K = 28: 6.5 ms, against
+// 24.2 ms with one voxel per lane over the whole box, FP64 accumulators
 // spilling and one wavefront per SIMD.
 constexpr int kBuildWaves = 4;
 constexpr int kBuildVox = 32;
@@ -453,7 +453,8 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_build(const float* __restr
   }
 }
 
-// k_build with t' in LDS, for balls that fit it (kBuildBall floats, r up to 17):
+// k_build with t' in LDS, for balls that fit it (kBuildBall floats, r up to 17) and more
+// than a few rotations:
 // the gathers of t' then cost LDS cycles instead of L2 lines.
 //
 // Slice dz of the ball is kept as the square |dy| <= h + 1, -h - 2 <= dx <= h + 2
@@ -463,7 +464,7 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_build(const float* __restr
 // A workgroup of 16 wavefronts fills a CU: wavefront w takes voxel group w % 4 (32
 // voxels) and every fourth block of kLdsChunk rotations, whose monomials the four
 // wavefronts of a group share; the totals meet in LDS at the end as in k_build.
-// 40^3, r = 17, 24 000 rotations, K = 28: 3.1 ms, 6.6 ms from global memory.
+// 40^3, r = 17, 24 000 rotations, K = 28: 3.0 ms, 6.6 ms from global memory.
 constexpr int kLdsChunk = 32;
 constexpr int kLdsWaves = 16;
 constexpr int kLdsGroups = 4;                     // rotation groups = voxel groups

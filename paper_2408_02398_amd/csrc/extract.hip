@@ -594,7 +594,7 @@ __global__ __launch_bounds__(256) void k_prepare(ExtractArgs a, Items it, int wr
 // loop holds nothing else: an ended lane keeps its answer until the refill writes
 // it, the queue is uniform, and the refill (as many instructions as two steps, for
 // a few lanes) has neither a division nor a square root.  97^3 voxels of degree 6:
-// 4.09 -> 3.18 ms with score and polish.
+// 4.07 -> 3.13 ms with score and polish.
 struct RunArgs {
   Items items;
   int per_item;   // R

@@ -7,9 +7,11 @@
 // access is a 128-byte segment).  Templates, which are nonzero only in their
 // first L z planes, stop after the Y pass and keep just those planes.
 // Inverse = Z pass with the spectral product fused in (one read of G per tile
-// for all components; each template column's z transform formed in registers
-// from its L stored values), Y pass, X pass with the C2R merge, 1/N^3 scale,
-// weight map, crop and dtype conversion fused into the store.
+// for all components from 192 on, for parts of them below; each template column's z
+// transform formed in registers from its L stored values), Y pass, X pass with the
+// C2R merge, 1/N^3 scale, weight map, crop and dtype conversion fused into the store
+// (k_c2c_rows and k_c2r_x; up to 160 both in k_c2r_plane, a plane in LDS).  The inverse
+// of the two local sums forms w in its X pass from 192 on.
 #include <algorithm>
 
 #include "internal.hpp"
